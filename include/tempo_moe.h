@@ -303,7 +303,7 @@ int tempo_moe_combine(const tempo_moe_shape* shape, const int32_t* pair_row, con
  * stage_events: nullable host array of TEMPO_STAGE_EVENTS (8) hipEvent_t
  * (created by the caller; each entry nullable) recorded on `stream` before
  * stage 1, after stage 1, right before the gate/up GEMM kernel (after the
- * activation pack of the 256-row large-tile kernels), after it, after the
+ * activation pack of the wide- and large-tile kernels), after it, after the
  * whole gate/up step (split-item fixup and, for fp8, the re-quantisation of
  * h), after the down GEMM kernel, after the whole down step and after
  * stage 3, for per-stage and per-kernel timing.

@@ -69,7 +69,11 @@ hipError_t launch_bm(const tempo_moe_shape& s, const tempo_dispatch_out& d, cons
 }  // namespace
 
 bool experts_gather_rows(const tempo_moe_shape& s, const Layout& L) {
-  // the large-tile kernels pack the token rows themselves
+  // the wide- and large-tile kernels pack the token rows themselves
+  return L.wide_tiles || stream_gathers_rows(s, L);
+}
+
+bool stream_gathers_rows(const tempo_moe_shape& s, const Layout& L) {
   if (experts_big_supported(s) || experts_big_f8_supported(s)) return true;
   // upper bound of the M-tiles one workgroup range of the gate/up GEMM spans
   const int grid = persistent_grid(1);
@@ -87,6 +91,7 @@ bool experts_gather_rows(const tempo_moe_shape& s, const Layout& L) {
 hipError_t launch_experts_bf16(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,
                                const void* x_rows, void* y_perm, char* ws, const Layout& L, bool timing, const hipEvent_t* ev,
                                hipStream_t st) {
+  if (L.wide_tiles) return launch_experts_wide(s, d, w, x_rows, nullptr, y_perm, ws, L, timing, ev, st);
   if (s.m_tile == 128) return launch_bm<128>(s, d, w, x_rows, y_perm, ws, L, timing, ev, st);
   if (s.m_tile == 64) return launch_bm<64>(s, d, w, x_rows, y_perm, ws, L, timing, ev, st);
   if (s.m_tile == 256) {

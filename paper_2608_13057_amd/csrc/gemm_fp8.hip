@@ -140,11 +140,14 @@ hipError_t launch_bm(const tempo_moe_shape& s, const tempo_dispatch_out& d, cons
 
 bool experts_supported(const tempo_moe_shape&) { return true; }
 
-bool experts_reads_token_scales(const tempo_moe_shape& s) { return experts_big_f8_supported(s); }
+bool experts_reads_token_scales(const tempo_moe_shape& s, const Layout& L) {
+  return L.wide_tiles || experts_big_f8_supported(s);
+}
 
 hipError_t launch_experts_fp8(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,
                               const void* x_rows, const float* x_rows_scale, void* y_perm, char* ws, const Layout& L,
                               bool timing, const hipEvent_t* ev, hipStream_t st) {
+  if (L.wide_tiles) return launch_experts_wide(s, d, w, x_rows, x_rows_scale, y_perm, ws, L, timing, ev, st);
   if (s.dtype == TEMPO_FP8_E4M3_UE8M0) {
     if (experts_big_f8_supported(s))
       return launch_experts_big_f8(s, d, w, x_rows, x_rows_scale, y_perm, ws, L, timing, ev, st);

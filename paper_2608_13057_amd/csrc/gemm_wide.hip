@@ -1,0 +1,715 @@
+// Stage 2 for batches whose slots hold many rows, whatever the M-tile of
+// stage 1 and for all three element types: both GEMMs on items of up to 256
+// rows x 256 packed weight rows, computed by eight wavefronts.
+//
+// * Rows are taken per slot, not per M-tile: a slot's rows are contiguous, so
+//   "wide tile" u of a slot is its rows 256 u .. 256 u + 255.  The M-tile only
+//   sets the padding between slots.
+// * Operands in MFMA operand order: the weights from tempo_moe_pack_weights,
+//   the activation rows of every wide tile from k_pack_wide, and h from the
+//   gate/up epilogue.  Per 128-byte contraction step a packed tile is 32 KB;
+//   rows 32b .. 32b + 31 form the 4 KB piece b, four 1 KB loads j in which
+//   lane l holds 16-byte chunk c(j, l) of row 32b + l % 32 (fp8
+//   c = 4 (j / 2) + 2 (l / 32) + j % 2, bf16 c = 2 j + l / 32), like the packed
+//   weights.  fp8 activation scales go beside it as 256 fp32 per tile and step.
+// * Eight wavefronts, two per SIMD: wavefront (wm, wn) takes the row blocks
+//   2 i + wm (i = 0 .. 3) against the weight rows 64 wn .. 64 wn + 63 (two
+//   pieces j), 128 accumulator registers per lane.  With fp32 block scales a
+//   step's product of a row block has to be scaled in VALU before it is added
+//   (acc += p * (sA * sW), 16 FMAs per 32 x 32 tile), so the accumulators have
+//   to be VGPRs; the second wavefront of a SIMD keeps the matrix pipe busy
+//   meanwhile.  The weights are the MFMAs' first operand: a lane owns one
+//   token row, so sA is one register per row block.
+// * Operands stream through LDS by DMA: two slots of weights (32 KB, one step
+//   each) and five half-steps of activations (16 KB: row blocks 0 .. 3, then
+//   4 .. 7).  A step is two phases with a barrier each; a wavefront holds its
+//   weight fragments of the step in registers, so the weight slot is refilled
+//   (step k + 2) in the second phase, and a half-step of activations as soon
+//   as its phase is over (five half-steps ahead): 100 KB or so in flight.  The
+//   stream runs on across items.
+// * Items are dealt as in the other large-tile kernels: tiles sorted by live
+//   row blocks, groups of 4 tiles x all weight blocks, runs per XCD, rounds
+//   alternately forwards and backwards.  Row blocks of padding only are not
+//   computed.  Items are never split: a row's sums run over its steps in
+//   order, so its result depends on its own inputs alone.
+// * gate/up epilogue: SwiGLU; fp8: the amax of each row over the item's 128
+//   h columns (one contraction step of the down GEMM), the scale amax / 448
+//   (power of two for UE8M0) and the e4m3 codes, packed for the down GEMM.
+#include <algorithm>
+
+#include "gemm_stream.h"
+
+namespace tempo {
+namespace {
+
+using namespace gemm;
+
+constexpr int WT_M = 256;                    // rows of a wide tile
+constexpr int WT_THREADS = 512;              // eight wavefronts
+constexpr int WT_STEP = 32 * 1024;           // bytes of a step of 256 rows
+constexpr int WT_UNIT = WT_STEP / 2;         // a half-step of activations: row blocks 0..3 or 4..7
+constexpr int WT_NA = 5;                     // activation half-steps in the ring
+constexpr int WT_SCW = 160;                  // scale bytes of one wavefront: 32 rows, then two weight blocks
+constexpr int WT_SC = 8 * WT_SCW;            // scales of a step (fp8)
+constexpr int WT_A = 0;                      // LDS ring: activations,
+constexpr int WT_W = WT_NA * WT_UNIT;        //   weights (2 slots),
+constexpr int WT_S = WT_W + 2 * WT_STEP;     //   scales (2 slots)
+constexpr int WT_RING = WT_S + 2 * WT_SC;
+constexpr int WT_MAX_SORT = 1024;            // tiles the cost-ordered list covers (beyond: tile order)
+constexpr int WT_GM = 4;                     // tiles per group of the item order
+
+enum WideType : int { kWideF8 = 0, kWideMX = 1, kWideBf16 = 2 };
+
+struct WideArgs {
+  const char* A;          // packed activation tiles
+  const float* A_sc;      // fp8: [tile][step][256]
+  const char* W;          // packed weights
+  size_t w_slot_bytes;
+  const float* Wsp;       // fp8: packed weight scales [slot][block][step][4]
+  size_t ws_slot_floats;
+  const uint64_t* wtab;
+  int wfield, sfield;
+  char* C;                // gate/up: packed h tiles; down: y_perm rows (bf16)
+  float* C_sc;            // gate/up, fp8: h scales [tile][step][256]
+  const int32_t* slot_counts;
+  const int32_t* slot_offsets;
+  int S, KT, NB, max_tiles;  // KT: steps per item; NB: 128-row weight blocks
+  int row_cap;
+  int ld_out;             // down: bytes of a row of y_perm
+  uint64_t* t0;
+  uint64_t* t1;
+  int timing;
+};
+
+// Slot tables in LDS.  (Counts are held to the slot's own padded rows and the
+// row buffers: stage 2 can be called on a caller's counts and offsets.)
+__device__ __forceinline__ void wide_slots(const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets,
+                                           int S, int row_cap, int32_t* off, int32_t* cnt, int tid, int nthreads) {
+  for (int s = tid; s < S; s += nthreads) {
+    const int o = min(max(offsets[s], 0), row_cap), e = min(offsets[s + 1], row_cap);
+    off[s] = o;
+    cnt[s] = max(0, min(counts[s], e - o));
+  }
+}
+
+// Wide tiles of the slots before s (st has S + 1 entries), by one wavefront.
+__device__ __forceinline__ void wide_prefix(const int32_t* cnt, int32_t* st, int S) {
+  const int l = threadIdx.x & 63;
+  int w[4], run = 0;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int s = 4 * l + i;
+    run += s < S ? (cnt[s] + WT_M - 1) / WT_M : 0;
+    w[i] = run;
+  }
+  int incl = run;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(incl, d);
+    if (l >= d) incl += o;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+    if (4 * l + i < S) st[4 * l + i + 1] = incl - run + w[i];
+  if (l == 0) st[0] = 0;
+}
+
+// Slot of wide tile t (the last s with st[s] <= t).
+__device__ __forceinline__ int wide_slot(const int32_t* st, int S, int t) {
+  int lo = 0, hi = S;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (st[mid] <= t) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// The activation rows of every wide tile in packed order, from token rows
+// (gather: row r is token row_token[r] of A) or from permuted rows; fp8
+// scales from the token rows' own [token][KT] (gather) or the block-major
+// [KT][row_cap] ones of stage 1.  Padding rows of a live row block are zero
+// with scale 1; row blocks of padding only are not written.  One (tile, step)
+// block of 32 KB per workgroup of a fixed grid at a time.  x_perm, x_perm_sc
+// (each nullable): the stage-1 outputs of the same rows, which the forward
+// leaves to this kernel.
+template <bool FP8>
+__global__ __launch_bounds__(256) void k_pack_wide(const char* __restrict__ A, const float* __restrict__ A_scale,
+                                                   int gather, int row_cap, const int32_t* __restrict__ row_token,
+                                                   const int32_t* __restrict__ slot_counts,
+                                                   const int32_t* __restrict__ slot_offsets, int S, int max_tiles,
+                                                   int KT, char* __restrict__ out, float* __restrict__ out_sc,
+                                                   char* __restrict__ x_perm, float* __restrict__ x_perm_sc) {
+  __shared__ int32_t s_cnt[kMaxS], s_off[kMaxS], s_st[kMaxS + 1];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  wide_slots(slot_counts, slot_offsets, S, row_cap, s_off, s_cnt, tid, 256);
+  __syncthreads();
+  if (tid < 64) wide_prefix(s_cnt, s_st, S);
+  __syncthreads();
+  const int blocks = min(s_st[S], max_tiles) * KT;
+#pragma unroll 1
+  for (int blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+    const int tile = blk / KT, kt = blk - tile * KT;
+    const int slot = __builtin_amdgcn_readfirstlane(wide_slot(s_st, S, tile));
+    const int sub = (tile - s_st[slot]) * WT_M;
+    const int row0 = s_off[slot] + sub, nvalid = min(WT_M, s_cnt[slot] - sub);
+    int tok[2];
+#pragma unroll
+    for (int pb = 0; pb < 2; pb++) {
+      const int r = 32 * (2 * w + pb) + (lane & 31);
+      tok[pb] = r < nvalid ? (gather ? row_token[row0 + r] : row0 + r) : -1;
+    }
+    i32x4 v[2][4];
+#pragma unroll
+    for (int pb = 0; pb < 2; pb++) {
+      if (32 * (2 * w + pb) >= nvalid) continue;
+      const size_t src = (size_t)max(tok[pb], 0) * KT * 128 + kt * 128;
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int c = FP8 ? 4 * (j >> 1) + 2 * (lane >> 5) + (j & 1) : 2 * j + (lane >> 5);
+        v[pb][j] = *reinterpret_cast<const i32x4*>(A + src + c * 16);
+      }
+    }
+    float sc = 1.f;
+    if (FP8 && tid < nvalid) {
+      if (gather) sc = A_scale[(size_t)max(row_token[row0 + tid], 0) * KT + kt];
+      else sc = A_scale[(size_t)kt * row_cap + row0 + tid];
+    }
+    char* dst = out + (size_t)blk * WT_STEP;
+#pragma unroll
+    for (int pb = 0; pb < 2; pb++) {
+      const int b = 2 * w + pb;
+      if (32 * b >= nvalid) continue;
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const i32x4 z = {0, 0, 0, 0};
+        *reinterpret_cast<i32x4*>(dst + b * 4096 + j * 1024 + lane * 16) = tok[pb] < 0 ? z : v[pb][j];
+      }
+      if (x_perm && tok[pb] >= 0) {
+        char* xr = x_perm + (size_t)(row0 + 32 * b + (lane & 31)) * KT * 128 + kt * 128;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          const int c = FP8 ? 4 * (j >> 1) + 2 * (lane >> 5) + (j & 1) : 2 * j + (lane >> 5);
+          *reinterpret_cast<i32x4*>(xr + c * 16) = v[pb][j];
+        }
+      }
+    }
+    if (FP8) out_sc[(size_t)blk * WT_M + tid] = sc;
+    if (FP8 && x_perm_sc && tid < nvalid) x_perm_sc[(size_t)kt * row_cap + row0 + tid] = sc;
+  }
+}
+
+// 16 bytes per lane of `lanes` from per-lane addresses into LDS at
+// lds + 16 * lane (EXEC switched inside the statement, as in
+// lds_dma16s_lanes).
+__device__ __forceinline__ void lds_dma16v_lanes(const void* gptr, uint32_t lds, uint64_t lanes) {
+  uint64_t saved;
+  asm volatile(
+      "s_mov_b64 %0, exec\n\t"
+      "s_mov_b64 exec, %3\n\t"
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off\n\t"
+      "s_mov_b64 exec, %0"
+      : "=&s"(saved)
+      : "v"(gptr), "s"(lds), "s"(lanes)
+      : "memory", "m0");
+}
+
+template <int DT, bool GATEUP>
+__global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
+  constexpr bool F8 = DT != kWideBf16, MX = DT == kWideMX;
+  constexpr int SL = F8 ? 1 : 0;             // scale loads per wavefront and step
+  constexpr int IN_FLIGHT = 10 + SL;         // loads that may be outstanding at a phase end (below)
+  __shared__ __attribute__((aligned(1024))) char ring[WT_RING];
+  __shared__ float xamax[4][WT_M];
+  __shared__ int32_t s_off[kMaxS], s_cnt[kMaxS], s_st[kMaxS + 1];
+  __shared__ uint32_t s_ord[WT_MAX_SORT];    // slot | (wide tile within the slot) << 8, in cost order
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave & 1, wn = wave >> 1;
+  wide_slots(p.slot_counts, p.slot_offsets, p.S, p.row_cap, s_off, s_cnt, tid, WT_THREADS);
+  __syncthreads();
+  if (tid < 64) wide_prefix(s_cnt, s_st, p.S);
+  __syncthreads();
+  const int NT = __builtin_amdgcn_readfirstlane(min(s_st[p.S], p.max_tiles));
+  const bool sorted = NT <= WT_MAX_SORT;
+  auto tile_desc = [&](int t) {
+    const int s = wide_slot(s_st, p.S, t);
+    return (uint32_t)s | (uint32_t)(t - s_st[s]) << 8;
+  };
+  if (sorted && tid < 64) {
+    // stable counting sort by live row blocks, most first
+    auto live_of = [&](uint32_t d) { return (min(WT_M, s_cnt[d & 255] - (int)(d >> 8) * WT_M) + 31) >> 5; };
+    const uint64_t below = (1ull << lane) - 1;
+    int pos = 0;
+    for (int c = 8; c >= 1; c--)
+      for (int t0 = 0; t0 < NT; t0 += 64) {
+        const int t = t0 + lane;
+        const uint32_t d = t < NT ? tile_desc(t) : 0;
+        const uint64_t m = __ballot(t < NT && live_of(d) == c);
+        if ((m >> lane) & 1) s_ord[pos + __popcll(m & below)] = d;
+        pos += __popcll(m);
+      }
+  }
+  __syncthreads();
+
+  const int KT = p.KT;
+  const int NBT = (p.NB + 1) / 2;  // items per tile
+  const int items = NT * NBT;
+  const int G = gridDim.x;
+  const int lin0 = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
+  const int full = items / G;
+  const int my_items = full + (((full & 1) ? G - 1 - lin0 : lin0) < items - full * G ? 1 : 0);
+  if (my_items == 0) return;
+  // item n of this workgroup: slot | sub << 8, and the pair of weight blocks
+  auto item_of = [&](int n, int& nbt) {
+    const int it = n * G + ((n & 1) ? G - 1 - lin0 : lin0);
+    const int grp = it / (WT_GM * NBT), w_in = it - grp * (WT_GM * NBT);
+    const int gm = min(WT_GM, NT - grp * WT_GM);
+    nbt = w_in / gm;
+    const int t = grp * WT_GM + (w_in - nbt * gm);
+    return (uint32_t)__builtin_amdgcn_readfirstlane(sorted ? s_ord[t] : tile_desc(t));
+  };
+  auto uni = [](uint64_t v) {
+    return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+  };
+
+  // ---- load side ----
+  // Activations: half-step ca_h of step ca_k of item ca_n; this wavefront's
+  // 2 KB of it: row block 4 h + wave / 2, loads 2 (wave & 1) and + 1.  A row
+  // block of padding only is replaced by block 0 of the tile (loaded again,
+  // read by nobody).  Weights (and scales): step cw_k of item cw_n; piece wave
+  // of the eight.  Past the last item the last one is loaded again, so that
+  // every phase issues the same number of loads.
+  const uint32_t ring_lds = lds_addr(ring);
+  const uint32_t lane16 = lane * 16;
+  int ca_n = -1, ca_k = KT - 1, ca_h = 1, ca_u = WT_NA - 1;
+  int cw_n = -1, cw_k = KT - 1, cw_s = 1;
+  uint64_t a_base = 0, w_base = 0;
+  uint32_t a_blk[2] = {0, 0};
+  const char* s_ptr = nullptr;
+  uint32_t s_inc = 0;
+  auto load_a = [&]() {
+    if (++ca_u == WT_NA) ca_u = 0;
+    if ((ca_h ^= 1) == 0 && ++ca_k == KT) {
+      ca_k = 0;
+      ca_n = min(ca_n + 1, my_items - 1);
+      int nbt;
+      const uint32_t d = item_of(ca_n, nbt);
+      const int slot = d & 255, sub = d >> 8;
+      const int live = (min(WT_M, s_cnt[slot] - sub * WT_M) + 31) >> 5;
+      a_base = uni((uint64_t)(uintptr_t)p.A + (size_t)(s_st[slot] + sub) * KT * WT_STEP + (wave & 1) * 2048);
+#pragma unroll
+      for (int h = 0; h < 2; h++) {
+        const int b = 4 * h + (wave >> 1);
+        a_blk[h] = __builtin_amdgcn_readfirstlane(b < live ? b * 4096 : 0);
+      }
+    }
+    const char* src = reinterpret_cast<const char*>(a_base) + (size_t)ca_k * WT_STEP + (ca_h ? a_blk[1] : a_blk[0]);
+    const uint32_t dst = ring_lds + WT_A + ca_u * WT_UNIT + wave * 2048;
+    lds_dma16s(src, lane16, dst);
+    lds_dma16s(src, lane16 + 1024, dst + 1024);
+  };
+  auto load_w = [&]() {
+    cw_s ^= 1;
+    if (++cw_k == KT) {
+      cw_k = 0;
+      cw_n = min(cw_n + 1, my_items - 1);
+      int nbt;
+      const uint32_t d = item_of(cw_n, nbt);
+      const int slot = d & 255, sub = d >> 8;
+      // (the second block of the last item of an odd number of blocks is the first again)
+      const int blk = min(2 * nbt + (wave >> 2), p.NB - 1);
+      w_base = uni((uint64_t)(uintptr_t)slot_tensor(p.W, p.w_slot_bytes, p.wtab, p.wfield, slot) +
+                   (size_t)blk * KT * B_BYTES + (wave & 3) * 4096);
+      if (F8) {
+        // lanes 0 .. 7: the scales of rows 32 wave .. 32 wave + 31; lanes 8, 9: those of the two weight blocks
+        const char* ws = slot_tensor(reinterpret_cast<const char*>(p.Wsp), p.ws_slot_floats * 4, p.wtab, p.sfield, slot);
+        const char* as = reinterpret_cast<const char*>(p.A_sc + ((size_t)(s_st[slot] + sub) * KT) * WT_M + 32 * wave);
+        s_ptr = lane < 8 ? as + lane16 : ws + (size_t)min(2 * nbt + (lane == 9 ? 1 : 0), p.NB - 1) * KT * 16;
+        s_inc = lane < 8 ? WT_M * 4 : 16;
+      }
+    }
+    const char* src = reinterpret_cast<const char*>(w_base) + (size_t)cw_k * B_BYTES;
+    const uint32_t dst = ring_lds + WT_W + cw_s * WT_STEP + wave * 4096;
+#pragma unroll
+    for (int j = 0; j < 4; j++) lds_dma16s(src, lane16 + j * 1024, dst + j * 1024);
+    if (F8) {
+      lds_dma16v_lanes(s_ptr, ring_lds + WT_S + cw_s * WT_SC + wave * WT_SCW, 0x3FFull);
+      s_ptr += s_inc;
+    }
+  };
+
+  // ---- compute side ----
+  f32x16 acc[4][2];
+  i32x8 fb[2][2];
+  int u_rd = 0, w_rd = 0;  // ring positions of the phase / step being read
+  float sa[4], sw0 = 1.f, sw1 = 1.f;
+  auto rd8 = [&](const char* s) {
+    const i32x4 lo = *reinterpret_cast<const i32x4*>(s);
+    const i32x4 hi = *reinterpret_cast<const i32x4*>(s + 1024);
+    return (i32x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  };
+  const char* const my_a = ring + WT_A + wm * 4096 + lane16;
+  const char* const my_w = ring + WT_W + wn * 8192 + lane16;
+  const char* const my_s = ring + WT_S + wm * WT_SCW + (lane & 31) * 4;
+  auto read_w = [&]() {
+    const char* s = my_w + w_rd * WT_STEP;
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int h = 0; h < 2; h++) fb[j][h] = rd8(s + j * 4096 + h * 2048);
+  };
+  auto read_s = [&]() {
+    const char* s = my_s + w_rd * WT_SC;
+#pragma unroll
+    for (int i = 0; i < 4; i++) sa[i] = *reinterpret_cast<const float*>(s + 2 * i * WT_SCW);
+    const float2 v = *reinterpret_cast<const float2*>(ring + WT_S + w_rd * WT_SC + 128 + 16 * (wn >> 1));
+    sw0 = v.x;
+    sw1 = GATEUP ? v.y : v.x;
+  };
+  auto read_a = [&](i32x8 (&a)[2], int i) {
+    const char* s = my_a + u_rd * WT_UNIT + 8192 * (i & 1);
+#pragma unroll
+    for (int h = 0; h < 2; h++) a[h] = rd8(s + h * 2048);
+  };
+  auto ue = [](float s) { return (int)((__float_as_uint(s) >> 23) & 0xFF); };
+  // acc of row block i += its rows times this wavefront's weight rows, over one step
+  auto mul = [&](const i32x8 (&a)[2], int i) {
+    if constexpr (DT == kWideBf16) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) {
+        const i32x8& av = a[ks >> 1];
+        const int o = 4 * (ks & 1);
+        const i32x4 ax = {av[o], av[o + 1], av[o + 2], av[o + 3]};
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          const i32x8& bv = fb[j][ks >> 1];
+          const i32x4 bx = {bv[o], bv[o + 1], bv[o + 2], bv[o + 3]};
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(reinterpret_cast<const bf16x8&>(bx),
+                                                              reinterpret_cast<const bf16x8&>(ax), acc[i][j], 0, 0, 0);
+        }
+      }
+    } else if constexpr (MX) {
+      const int ea = ue(sa[i]);
+      const int eb = GATEUP ? ((lane & 16) ? ue(sw1) : ue(sw0)) : ue(sw0);
+#pragma unroll
+      for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+          acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][h], a[h], acc[i][j], 0, 0, 0, eb, 0, ea);
+    } else {
+      f32x16 pp[2];
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        const f32x16 z = {};
+        pp[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][0], a[0], z, 0, 0, 0, 127, 0, 127);
+        pp[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][1], a[1], pp[j], 0, 0, 0, 127, 0, 127);
+      }
+      // elements 0 .. 7 belong to the gate rows of a piece, 8 .. 15 to the up rows
+      const float s0 = sa[i] * sw0, s1 = sa[i] * sw1;
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) acc[i][j][e] += pp[j][e] * (e < 8 ? s0 : s1);
+    }
+  };
+  // The end of a phase: what the next one reads has landed and every
+  // wavefront is done reading what the next one's loads overwrite.  Loads
+  // complete in order, and a wavefront issues 2 (activations) in the first
+  // phase of a step and 4 + SL + 2 in the second (weights and scales of step
+  // k + 2, then activations), each needed 3 issues later: the second half of
+  // step k at the end of its first phase, the weights and the first half of
+  // step k + 1 at the end of the second.  2 + (6 + SL) + 2 loads follow
+  // either.
+  auto phase_end = [&]() {
+    wait_lgkm0();
+    __builtin_amdgcn_s_waitcnt(TEMPO_VMCNT_IMM(IN_FLIGHT));
+    barrier_nofence();
+    __builtin_amdgcn_sched_barrier(0);
+    if (++u_rd == WT_NA) u_rd = 0;
+  };
+
+  load_a();
+  load_w();
+  load_a();
+  load_a();
+  load_w();
+  load_a();
+  __builtin_amdgcn_s_waitcnt(TEMPO_VMCNT_IMM(IN_FLIGHT));
+  barrier_nofence();
+
+#pragma unroll 1
+  for (int n = 0; n < my_items; n++) {
+    int nbt;
+    const uint32_t d = item_of(n, nbt);
+    const int slot = d & 255, sub = d >> 8;
+    const int tile = __builtin_amdgcn_readfirstlane(s_st[slot] + sub);
+    const int row0 = __builtin_amdgcn_readfirstlane(s_off[slot] + sub * WT_M);
+    const int nvalid = __builtin_amdgcn_readfirstlane(min(WT_M, s_cnt[slot] - sub * WT_M));
+    // live row blocks 2 i + wm, i < nb, of this wavefront (none where its
+    // weight block is past the last one)
+    const int nb = 2 * nbt + (wn >> 1) < p.NB ? (((nvalid + 31) >> 5) + 1 - wm) >> 1 : 0;
+    const uint64_t tstart = p.timing ? __builtin_amdgcn_s_memrealtime() : 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+
+#pragma unroll 1
+    for (int k = 0; k < KT; k++) {
+#pragma unroll
+      for (int ph = 0; ph < 2; ph++) {
+        i32x8 a0[2], a1[2];
+        read_a(a0, 2 * ph);
+        if (ph == 0) {
+          read_w();
+          if (F8) read_s();
+        }
+        read_a(a1, 2 * ph + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (ph == 1) {
+          load_w();
+          w_rd ^= 1;
+        }
+        load_a();
+        __builtin_amdgcn_sched_barrier(0);
+        if (2 * ph < nb) mul(a0, 2 * ph);
+        if (2 * ph + 1 < nb) mul(a1, 2 * ph + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        phase_end();
+      }
+    }
+
+    // Epilogue.  Lane l of tile (i, j) holds token row 32 (2 i + wm) + l % 32
+    // and, in element e, packed weight row 8 (e / 4) + 4 (l / 32) + e % 4 of
+    // piece 2 (wn & 1) + j of block 2 nbt + wn / 2 (gate/up: rows 0 .. 15
+    // gate, 16 .. 31 up, so a column's gate and up are elements e and e + 8).
+    int lid;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lid));
+    const int l31 = lid & 31, hl = lid >> 5;
+    auto pack4 = [](float v0, float v1, float v2, float v3) {
+      uint2 w;
+      w.x = bf16x2_rne(v0, v1);
+      w.y = bf16x2_rne(v2, v3);
+      return w;
+    };
+    // lanes l and l + 32 hold 8-byte halves of 16-byte chunks; a swap gives
+    // lane l < 32 the whole chunk of w0, lane l + 32 that of w1
+    auto swap16 = [](uint2 w0, uint2 w1) {
+      const auto x = __builtin_amdgcn_permlane32_swap(w0.x, w1.x, false, false);
+      const auto y = __builtin_amdgcn_permlane32_swap(w0.y, w1.y, false, false);
+      return i32x4{(int)x[0], (int)y[0], (int)x[1], (int)y[1]};
+    };
+    if constexpr (GATEUP && F8) {
+      // h in place of the gate elements, and its amax over the item's 128
+      // columns: this lane's, the row's other lane's, the other wavefronts'
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        float m = 0.f;
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+          for (int e = 0; e < 8; e++) {
+            const float h = silu_mul(acc[i][j][e], acc[i][j][e + 8]);
+            acc[i][j][e] = h;
+            m = fmaxf(m, fabsf(h));
+          }
+        m = fmaxf(m, __shfl_xor(m, 32));
+        if (hl == 0) xamax[wn][32 * (2 * i + wm) + l31] = m;
+      }
+      wait_lgkm0();
+      barrier_nofence();
+      // chunk 4 (wn / 2) + 2 (wn & 1) + j of the row in step nbt of the down
+      // GEMM: load 2 (wn / 2) + j, lane l % 32 + 32 (wn & 1)
+      char* hb = p.C + ((size_t)tile * (p.NB / 2) + nbt) * WT_STEP + (2 * (wn >> 1) + hl) * 1024 +
+                 (32 * (wn & 1) + l31) * 16;
+      float* hs = p.C_sc + ((size_t)tile * (p.NB / 2) + nbt) * WT_M;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        if (i >= nb) continue;
+        const int r = 32 * (2 * i + wm) + l31;
+        const float mm = fmaxf(fmaxf(xamax[0][r], xamax[1][r]), fmaxf(xamax[2][r], xamax[3][r]));
+        float sc = mm > 0.f ? mm / 448.0f : 1.0f;
+        if (MX && mm > 0.f) {
+          uint32_t bits = __float_as_uint(sc);
+          if (bits & 0x7FFFFFu) bits = (bits & 0xFF800000u) + 0x800000u;  // next power of two up
+          sc = __uint_as_float(bits);
+        }
+        if (wn == 0 && hl == 0) hs[r] = sc;
+        uint32_t w[2][2];
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          float q[8];
+#pragma unroll
+          for (int e = 0; e < 8; e++) q[e] = fminf(fmaxf(acc[i][j][e] / sc, -448.f), 448.f);
+#pragma unroll
+          for (int t = 0; t < 2; t++) {
+            uint32_t v = __builtin_amdgcn_cvt_pk_fp8_f32(q[4 * t], q[4 * t + 1], 0, false);
+            w[t][j] = __builtin_amdgcn_cvt_pk_fp8_f32(q[4 * t + 2], q[4 * t + 3], v, true);
+          }
+        }
+        // bytes 4 hl .. + 3 and 8 + 4 hl .. + 3 of the chunk; one swap per
+        // dword gives lane l the chunk of j = 0, lane l + 32 that of j = 1
+        const auto x = __builtin_amdgcn_permlane32_swap(w[0][0], w[0][1], false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(w[1][0], w[1][1], false, false);
+        *reinterpret_cast<i32x4*>(hb + (2 * i + wm) * 4096) = i32x4{(int)x[0], (int)x[1], (int)y[0], (int)y[1]};
+      }
+    } else if constexpr (GATEUP) {
+      // columns 64 (wn / 2) + 16 p + 8 q + 4 hl + m of the item's 128 (p the
+      // piece): chunk 2 p + q of step 2 nbt + wn / 2 of the down GEMM, i.e.
+      // load p, lane l % 32 + 32 q
+      char* hb = p.C + ((size_t)tile * p.NB + 2 * nbt + (wn >> 1)) * WT_STEP + 2 * (wn & 1) * 1024 + lid * 16;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        if (i >= nb) continue;
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          const f32x16& v = acc[i][j];
+          uint2 w[2];
+#pragma unroll
+          for (int q = 0; q < 2; q++)
+            w[q] = pack4(silu_mul(v[4 * q], v[4 * q + 8]), silu_mul(v[4 * q + 1], v[4 * q + 9]),
+                         silu_mul(v[4 * q + 2], v[4 * q + 10]), silu_mul(v[4 * q + 3], v[4 * q + 11]));
+          *reinterpret_cast<i32x4*>(hb + (2 * i + wm) * 4096 + j * 1024) = swap16(w[0], w[1]);
+        }
+      }
+    } else {
+      char* yb = p.C + (size_t)row0 * p.ld_out + (size_t)(256 * nbt + 64 * wn + 8 * hl) * 2;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        if (i >= nb) continue;
+        const int r = 32 * (2 * i + wm) + l31;
+        char* yr = yb + (size_t)r * p.ld_out;
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          const f32x16& v = acc[i][j];
+          uint2 w[4];
+#pragma unroll
+          for (int q = 0; q < 4; q++) w[q] = pack4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+          const i32x4 c0 = swap16(w[0], w[1]), c1 = swap16(w[2], w[3]);
+          if (r < nvalid) {  // padding rows of y_perm stay unwritten
+            *reinterpret_cast<i32x4*>(yr + (32 * j) * 2) = c0;
+            *reinterpret_cast<i32x4*>(yr + (32 * j + 16) * 2) = c1;
+          }
+        }
+      }
+    }
+    if (p.timing && tid == 0) {
+      const uint64_t tend = __builtin_amdgcn_s_memrealtime();
+      atomicMin(reinterpret_cast<unsigned long long*>(&p.t0[slot]), (unsigned long long)tstart);
+      atomicMax(reinterpret_cast<unsigned long long*>(&p.t1[slot]), (unsigned long long)tend);
+    }
+  }
+  // no DMA into this workgroup's LDS may outlive it
+  __builtin_amdgcn_s_waitcnt(TEMPO_VMCNT_IMM(0));
+}
+
+template <int DT>
+hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,
+                       const void* x_rows, const float* x_rows_scale, void* y_perm, char* ws, const Layout& L,
+                       bool timing, const hipEvent_t* ev, hipStream_t st) {
+  constexpr bool F8 = DT != kWideBf16;
+  constexpr int es = F8 ? 1 : 2;
+  const int grid = persistent_grid(1);
+  const int KTg = s.H * es / 128, KTd = s.I * es / 128;
+  auto mark = [&](int i) { return !ev || !ev[i] || hipEventRecord(ev[i], st) == hipSuccess; };
+  char* apack = ws + L.wide_a;
+  float* apack_sc = reinterpret_cast<float*>(ws + L.wide_a_sc);
+  const bool gather = x_rows != nullptr;
+  hipLaunchKernelGGL(k_pack_wide<F8>, dim3(persistent_grid(4)), dim3(256), 0, st,
+                     static_cast<const char*>(gather ? x_rows : d.x_perm), gather ? x_rows_scale : d.x_perm_scale,
+                     gather ? 1 : 0, L.row_cap, d.row_token, d.slot_counts, d.slot_offsets, s.S, L.wide_tiles, KTg,
+                     apack, apack_sc, gather && !stream_gathers_rows(s, L) ? static_cast<char*>(d.x_perm) : nullptr,
+                     gather && F8 ? d.x_perm_scale : nullptr);
+
+  WideArgs a{};
+  a.slot_counts = d.slot_counts;
+  a.slot_offsets = d.slot_offsets;
+  a.S = s.S;
+  a.max_tiles = L.wide_tiles;
+  a.row_cap = L.row_cap;
+  a.wtab = reinterpret_cast<const uint64_t*>(w.slot_table);
+  a.t0 = reinterpret_cast<uint64_t*>(ws + L.slot_t0);
+  a.t1 = reinterpret_cast<uint64_t*>(ws + L.slot_t1);
+  a.timing = timing ? 1 : 0;
+
+  WideArgs gu = a;
+  gu.A = apack;
+  gu.A_sc = apack_sc;
+  gu.W = static_cast<const char*>(w.w13);
+  gu.wfield = kFieldW13;
+  gu.sfield = kFieldW13Scale;
+  gu.w_slot_bytes = (size_t)2 * s.I * s.H * es;
+  gu.Wsp = w.w13_scale;
+  gu.ws_slot_floats = (size_t)(s.I / 64) * (s.H / 128) * 4;
+  gu.C = ws + L.wide_h;
+  gu.C_sc = reinterpret_cast<float*>(ws + L.wide_h_sc);
+  gu.KT = KTg;
+  gu.NB = s.I / 64;
+  if (!mark(0)) return hipErrorLaunchFailure;  // after the pack: the GEMM kernel alone is timed
+  hipLaunchKernelGGL((k_gemm_wide<DT, true>), dim3(grid), dim3(WT_THREADS), 0, st, gu);
+  if (!mark(1) || !mark(2)) return hipErrorLaunchFailure;
+
+  WideArgs dn = a;
+  dn.A = gu.C;
+  dn.A_sc = gu.C_sc;
+  dn.W = static_cast<const char*>(w.w2);
+  dn.wfield = kFieldW2;
+  dn.sfield = kFieldW2Scale;
+  dn.w_slot_bytes = (size_t)s.H * s.I * es;
+  dn.Wsp = w.w2_scale;
+  dn.ws_slot_floats = (size_t)(s.H / 128) * (s.I / 128) * 4;
+  dn.C = static_cast<char*>(y_perm);
+  dn.KT = KTd;
+  dn.NB = s.H / 128;
+  dn.ld_out = s.H * 2;
+  hipLaunchKernelGGL((k_gemm_wide<DT, false>), dim3(grid), dim3(WT_THREADS), 0, st, dn);
+  if (!mark(3)) return hipErrorLaunchFailure;
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// Where the wide tiles win: slots with enough rows, and enough items to fill
+// the chip.  The counts per slot are only known on the device; rows per
+// expert, T K / E, and the items that these make, stand for them (the same
+// for every plan and, but for the 256-row kernels, every M-tile, so a row's
+// result depends on neither).
+// Measured, forward us, other kernel -> wide tiles (18 or 36 slots, H 4096 /
+// 7168, uniform plan):
+//   fp8    16 rows per expert 128 -> 132, 32: 150 -> 146, 64: 181 -> 154,
+//          128: 254 -> 189, 256: 408 -> 255, 512 (18 slots): 713 -> 389;
+//          items 110: 94 -> 104, 139: 101 -> 100, 155: 91 -> 83,
+//          225: 153 -> 112
+//   UE8M0  32: 145 -> 139, 28 (36 slots): 327 -> 329, 64: 163 -> 146; its own
+//          256-row kernel, where that runs, is faster (320 -> 362 at 512)
+//   bf16   36: 213 -> 214, 65 (36 slots, M 128): 654 -> 690, 92: 304 -> 256,
+//          160: 324 -> 271, 265: 393 -> 368, 405: 495 -> 480, 512: 556 -> 567;
+//          items 156: 114 -> 131
+bool experts_wide_wanted(const tempo_moe_shape& s) {
+  if (experts_big_f8_supported(s)) return false;
+  const long long P = (long long)s.T * s.K;
+  // items of the gate/up GEMM, were the pairs spread evenly over the experts
+  const long long items = (s.S + P * s.S / (256ll * s.E)) * (s.I / 128);
+  if (s.dtype == TEMPO_BF16)
+    return P >= 80ll * s.E && items >= 200 && (P < 384ll * s.E || !experts_big_supported(s));
+  return P >= (s.dtype == TEMPO_FP8_E4M3 ? 32ll : 48ll) * s.E && items >= 150;
+}
+
+hipError_t launch_experts_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,
+                               const void* x_rows, const float* x_rows_scale, void* y_perm, char* ws, const Layout& L,
+                               bool timing, const hipEvent_t* ev, hipStream_t st) {
+  if (s.dtype == TEMPO_BF16)
+    return launch_wide<kWideBf16>(s, d, w, x_rows, x_rows_scale, y_perm, ws, L, timing, ev, st);
+  if (s.dtype == TEMPO_FP8_E4M3_UE8M0)
+    return launch_wide<kWideMX>(s, d, w, x_rows, x_rows_scale, y_perm, ws, L, timing, ev, st);
+  return launch_wide<kWideF8>(s, d, w, x_rows, x_rows_scale, y_perm, ws, L, timing, ev, st);
+}
+
+}  // namespace tempo

@@ -44,6 +44,10 @@ struct Layout {
   size_t part;        // [grid][8][m_tile][128] fp32 stage-2 partial tiles
   size_t fix;         // [grid][12] int32 stage-2 fixup records
   size_t total;
+  // wide-tile kernels (wide_tiles > 0): packed activation tiles and their
+  // scales, packed h and its scales (within the regions above)
+  size_t wide_a, wide_a_sc, wide_h, wide_h_sc;
+  int wide_tiles;     // most 256-row tiles of a batch
   int nblk;
   int row_cap;
 };
@@ -101,6 +105,14 @@ hipError_t launch_experts_big_f8(const tempo_moe_shape& s, const tempo_dispatch_
                                  const void* x_rows, const float* x_rows_scale, void* y_perm, char* ws,
                                  const Layout& L, bool timing, const hipEvent_t* ev, hipStream_t st);
 
+// Any element type and M-tile: both GEMMs on 256-row tiles taken per slot
+// (the wide-tile kernel), with the activation rows first packed into the
+// workspace.  Used where make_layout sets Layout::wide_tiles.
+bool experts_wide_wanted(const tempo_moe_shape& s);
+hipError_t launch_experts_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,
+                               const void* x_rows, const float* x_rows_scale, void* y_perm, char* ws, const Layout& L,
+                               bool timing, const hipEvent_t* ev, hipStream_t st);
+
 hipError_t launch_combine(const tempo_moe_shape& s, const int32_t* pair_row, const float* topk_w, const void* y_perm,
                           void* y, const int32_t* slot_counts, const uint64_t* t0, const uint64_t* t1,
                           uint64_t* slot_time_ns, hipStream_t st);
@@ -110,11 +122,14 @@ hipError_t launch_pack(const tempo_moe_shape& s, const tempo_expert_weights& nat
 
 // Whether stage 2 gathers the activation rows itself (through row_token)
 // rather than reading rows that stage 1 permuted into x_perm: true for the
-// large-tile kernel, whose pack step gathers them, and for the streaming
-// GEMM when every workgroup's range spans few enough M-tiles (the row tables
-// of its M-tiles sit in LDS).
+// wide- and large-tile kernels, whose pack step gathers them, and for the
+// streaming GEMM when every workgroup's range spans few enough M-tiles (the
+// row tables of its M-tiles sit in LDS).  stream_gathers_rows: the same
+// without the wide-tile kernels; where it is false the forward's x_perm is
+// written (by stage 1, or by the pack step of the wide-tile kernels).
 bool experts_gather_rows(const tempo_moe_shape& s, const Layout& L);
-bool experts_reads_token_scales(const tempo_moe_shape& s);
+bool stream_gathers_rows(const tempo_moe_shape& s, const Layout& L);
+bool experts_reads_token_scales(const tempo_moe_shape& s, const Layout& L);
 
 // Whether stage-2 kernels exist for this shape's element type and M-tile.
 bool experts_supported(const tempo_moe_shape& s);

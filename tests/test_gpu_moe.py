@@ -281,6 +281,58 @@ def test_forward_256_row_tiles_random_shapes(dtype, seed):
     _check_many_rows(dtype, err, err_m, same)
 
 
+@pytest.mark.parametrize("dtype,m_tile,H,reps", [("fp8", 64, 128, 1), ("fp8", 128, 384, 2), ("fp8", 256, 640, 1),
+                                                 ("fp8mx", 64, 384, 2), ("fp8mx", 256, 128, 1),
+                                                 ("bf16", 64, 128, 1), ("bf16", 128, 384, 2), ("bf16", 256, 384, 1)])
+def test_forward_wide_tiles(dtype, m_tile, H, reps):
+    """The wide-tile kernels at their edges: slots of no row, of every number
+    of live 32-row blocks of a 256-row tile, one row past a tile, and of two
+    to four tiles; contractions of one step (H 128, fp8) up; an odd number of
+    128-row weight blocks in the down GEMM; one or (reps 2) several items per
+    workgroup; stage 1 in every M-tile.  y on a token sample (one row of every
+    M-tile, every slot's last row, 200 random tokens) against the fp64 oracle
+    in exact and mirror modes; tokens with no local pair exactly zero; the
+    plain call of the three stages gives the same bits as the forward."""
+    import torch
+    from paper_2608_13057_amd import moe, synth
+
+    counts = [0, 1, 31, 33, 64, 65, 97, 129, 161, 193, 225, 255, 256, 257, 300, 520, 900] * reps
+    E, I = len(counts), 1152
+    ids = np.repeat(np.arange(E, dtype=np.int32), counts)
+    rng = np.random.default_rng(31)
+    rng.shuffle(ids)
+    T = ids.size
+    pl = synth.placement_local_hot(E, E, 1)  # a second slot for expert 0
+    w = rng.uniform(0.1, 1.0, (T, 1)).astype(np.float32)
+    wl = synth.Workload("wide", dtype, T, T - 2, 1, E, H, I, 0.0, pl, {"uniform": synth.plan_uniform(pl, E)},
+                        ids.reshape(T, 1), w, 0)
+    c = Case(wl, "uniform", m_tile)
+    print(f"[wide {dtype} M={m_tile} H={H} I={I}] running, {T} tokens", flush=True)
+    y, _ = _run_forward(c)
+    d = c.oracle_dispatch()
+    assert np.array_equal(to_host(c.disp.slot_counts), d["slot_counts"])
+    assert np.array_equal(to_host(c.disp.pair_row), d["pair_row"])
+    loc, none = _local_rows(d, c.T_valid)
+    assert np.all(y[none] == 0)
+    pick = np.union1d(tile_sample(d, m_tile, rng), rng.choice(loc, 200, replace=False))
+    sel = np.zeros(T, np.uint8)
+    sel[pick] = 1
+    got = bf16_to_f64(y)
+    ref = _oracle_y(c, d, "mirror", sel)
+    err_m, same = mirror_err_rows(got, ref, pick), identical_share(got[pick], ref[pick])
+    err = rel_err_rows(got, _oracle_y(c, d, "exact", sel), pick)
+    print(f"[wide {dtype} M={m_tile}] sampled {len(pick)} exact err={err:.2e} mirror err={err_m:.2e} "
+          f"identical={same:.4f}")
+    _check_many_rows(dtype, err, err_m, same)
+    moe.dispatch(c.shape, c.d_plan, c.d_ids, c.d_x, c.d_xs, c.disp, c.ws)
+    y_perm = torch.empty(c.ws.row_cap, H, dtype=torch.int16, device="cuda")
+    moe.experts(c.shape, c.disp, c.d_weights, y_perm, moe.Workspace(c.shape))
+    y2 = torch.empty(T, H, dtype=torch.int16, device="cuda")
+    moe.combine(c.shape, c.disp.pair_row, c.d_w, y_perm, y2)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(y2), y)
+
+
 @pytest.mark.parametrize("m_tile", [64, 128, 192, 256])
 @pytest.mark.parametrize("dtype", ["bf16", "fp8", "fp8mx"])
 def test_forward_stream_k_random_shapes(dtype, m_tile):
