@@ -20,18 +20,25 @@
 //   to be VGPRs; the second wavefront of a SIMD keeps the matrix pipe busy
 //   meanwhile.  The weights are the MFMAs' first operand: a lane owns one
 //   token row, so sA is one register per row block.
-// * Operands stream through LDS by DMA: two slots of weights (32 KB, one step
-//   each) and five half-steps of activations (16 KB: row blocks 0 .. 3, then
-//   4 .. 7).  A step is two phases with a barrier each; a wavefront holds its
-//   weight fragments of the step in registers, so the weight slot is refilled
-//   (step k + 2) in the second phase, and a half-step of activations as soon
-//   as its phase is over (five half-steps ahead): 100 KB or so in flight.  The
-//   stream runs on across items.
+// * Operands stream through LDS by DMA, 144 KB of ring in one of two forms.
+//   Tiles of more than four live row blocks: two slots of weights (32 KB, one
+//   step each) and five half-steps of activations (16 KB); a step has two
+//   barriers, fragments are read one row block ahead of their MFMAs, and each
+//   load is issued between two MFMAs.  Measured (18 slots H 4096 I 1536, 11486
+//   rows, gate/up GEMM): fp8 201 us with the loads in bursts and the fragments
+//   read at the start of a half-step, 181 like this (157 with neither loads
+//   nor fragment reads: the matrix pipes at 2.1 GHz, the rescale, barriers and
+//   the uneven last round of items are what is left); UE8M0 179 -> 163, bf16
+//   312 -> 294 (242 without loads and reads).  Smaller tiles: whole
+//   steps, three slots of 48 KB or, for one live row block, four of 36 KB,
+//   since these wait for their weights (64 or 96 KB of them in flight; 36
+//   slots H 7168 I 2048, 5024 rows, gate/up 297 -> 272, down 193 -> 155 us).
 // * Items are dealt as in the other large-tile kernels: tiles sorted by live
 //   row blocks, groups of 4 tiles x all weight blocks, runs per XCD, rounds
-//   alternately forwards and backwards.  Row blocks of padding only are not
-//   computed.  Items are never split: a row's sums run over its steps in
-//   order, so its result depends on its own inputs alone.
+//   alternately forwards and backwards; every second XCD works through its
+//   items from the small end.  Row blocks of padding only are not computed.
+//   Items are never split: a row's sums run over its steps in order, so its
+//   result depends on its own inputs alone.
 // * gate/up epilogue: SwiGLU; fp8: the amax of each row over the item's 128
 //   h columns (one contraction step of the down GEMM), the scale amax / 448
 //   (power of two for UE8M0) and the e4m3 codes, packed for the down GEMM.
@@ -53,8 +60,8 @@ constexpr int WT_SCW = 160;                  // scale bytes of one wavefront: 32
 constexpr int WT_SC = 8 * WT_SCW;            // scales of a step (fp8)
 constexpr int WT_A = 0;                      // LDS ring: activations,
 constexpr int WT_W = WT_NA * WT_UNIT;        //   weights (2 slots),
-constexpr int WT_S = WT_W + 2 * WT_STEP;     //   scales (2 slots)
-constexpr int WT_RING = WT_S + 2 * WT_SC;
+constexpr int WT_S = WT_W + 2 * WT_STEP;     //   scales (up to 4 slots)
+constexpr int WT_RING = WT_S + 4 * WT_SC;
 constexpr int WT_MAX_SORT = 1024;            // tiles the cost-ordered list covers (beyond: tile order)
 constexpr int WT_GM = 4;                     // tiles per group of the item order
 
@@ -216,11 +223,59 @@ __device__ __forceinline__ void lds_dma16v_lanes(const void* gptr, uint32_t lds,
       : "memory", "m0");
 }
 
+// Load J of 1 KB pieces that are consecutive in memory and in LDS (the
+// instruction's offset counts in both addresses).
+template <int J>
+__device__ __forceinline__ void lds_dma16s_at(uint64_t sbase, uint32_t voff, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(voff),
+      "s"(sbase), "s"(lds), "n"(J * 1024)
+      : "memory", "m0");
+}
+// Four (two) of them, with one M0.
+__device__ __forceinline__ void lds_dma16s_x4(uint64_t sbase, uint32_t voff, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %1\n\t"
+      "global_load_lds_dwordx4 %0, %1 offset:1024\n\t"
+      "global_load_lds_dwordx4 %0, %1 offset:2048\n\t"
+      "global_load_lds_dwordx4 %0, %1 offset:3072" ::"v"(voff),
+      "s"(sbase), "s"(lds)
+      : "memory", "m0");
+}
+__device__ __forceinline__ void lds_dma16s_x2(uint64_t sbase, uint32_t voff, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %1\n\t"
+      "global_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(voff),
+      "s"(sbase), "s"(lds)
+      : "memory", "m0");
+}
+// the same two, or, where on is 0, two loads of no lane (they only count)
+__device__ __forceinline__ void lds_dma16s_x2_if(uint64_t sbase, uint32_t voff, uint32_t lds, int on) {
+  uint64_t saved;
+  asm volatile(
+      "s_mov_b64 %0, exec\n\t"
+      "s_cmp_lg_u32 %4, 0\n\t"
+      "s_cselect_b64 exec, exec, 0\n\t"
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, %3\n\t"
+      "global_load_lds_dwordx4 %1, %3 offset:1024\n\t"
+      "s_mov_b64 exec, %0"
+      : "=&s"(saved)
+      : "v"(voff), "s"(lds), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(on))
+      : "memory", "m0", "scc");
+}
+
 template <int DT, bool GATEUP>
 __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
   constexpr bool F8 = DT != kWideBf16, MX = DT == kWideMX;
   constexpr int SL = F8 ? 1 : 0;             // scale loads per wavefront and step
-  constexpr int IN_FLIGHT = 10 + SL;         // loads that may be outstanding at a phase end (below)
   __shared__ __attribute__((aligned(1024))) char ring[WT_RING];
   __shared__ float xamax[4][WT_M];
   __shared__ int32_t s_off[kMaxS], s_cnt[kMaxS], s_st[kMaxS + 1];
@@ -239,19 +294,38 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     const int s = wide_slot(s_st, p.S, t);
     return (uint32_t)s | (uint32_t)(t - s_st[s]) << 8;
   };
+  auto live_of = [&](uint32_t d) { return (min(WT_M, s_cnt[d & 255] - (int)(d >> 8) * WT_M) + 31) >> 5; };
   if (sorted && tid < 64) {
-    // stable counting sort by live row blocks, most first
-    auto live_of = [&](uint32_t d) { return (min(WT_M, s_cnt[d & 255] - (int)(d >> 8) * WT_M) + 31) >> 5; };
+    // stable counting sort by live row blocks, most first (descriptors and
+    // classes once per tile, held in the ring's bytes between the passes)
+    uint32_t* const tmp = reinterpret_cast<uint32_t*>(ring);
     const uint64_t below = (1ull << lane) - 1;
-    int pos = 0;
-    for (int c = 8; c >= 1; c--)
-      for (int t0 = 0; t0 < NT; t0 += 64) {
-        const int t = t0 + lane;
-        const uint32_t d = t < NT ? tile_desc(t) : 0;
-        const uint64_t m = __ballot(t < NT && live_of(d) == c);
-        if ((m >> lane) & 1) s_ord[pos + __popcll(m & below)] = d;
-        pos += __popcll(m);
+    int pos[9] = {};
+    for (int t0 = 0; t0 < NT; t0 += 64) {
+      const int t = t0 + lane;
+      const uint32_t d = t < NT ? tile_desc(t) : 0;
+      const int c = t < NT ? live_of(d) : 0;
+      tmp[t] = d | (uint32_t)c << 27;
+#pragma unroll
+      for (int k = 1; k <= 8; k++) pos[k] += __popcll(__ballot(c == k));
+    }
+    int run = 0;
+#pragma unroll
+    for (int k = 8; k >= 1; k--) {
+      const int m = pos[k];
+      pos[k] = run;
+      run += m;
+    }
+    for (int t0 = 0; t0 < NT; t0 += 64) {
+      const uint32_t v = tmp[t0 + lane];
+      const int c = v >> 27;
+#pragma unroll
+      for (int k = 1; k <= 8; k++) {
+        const uint64_t m = __ballot(c == k);
+        if (c == k) s_ord[pos[k] + __popcll(m & below)] = v & 0x7FFFFFF;
+        pos[k] += __popcll(m);
       }
+    }
   }
   __syncthreads();
 
@@ -263,152 +337,144 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
   const int full = items / G;
   const int my_items = full + (((full & 1) ? G - 1 - lin0 : lin0) < items - full * G ? 1 : 0);
   if (my_items == 0) return;
-  // item n of this workgroup: slot | sub << 8, and the pair of weight blocks
+  // item n of this workgroup: slot | sub << 8, and the pair of weight blocks.
+  // Every second XCD takes its items the other way round, the small ones
+  // first: tiles of few rows wait for their weights, full ones for the matrix
+  // pipes, and the two kinds run side by side.
   auto item_of = [&](int n, int& nbt) {
+    if (blockIdx.x & 1) n = my_items - 1 - n;
     const int it = n * G + ((n & 1) ? G - 1 - lin0 : lin0);
     const int grp = it / (WT_GM * NBT), w_in = it - grp * (WT_GM * NBT);
     const int gm = min(WT_GM, NT - grp * WT_GM);
     nbt = w_in / gm;
     const int t = grp * WT_GM + (w_in - nbt * gm);
-    return (uint32_t)__builtin_amdgcn_readfirstlane(sorted ? s_ord[t] : tile_desc(t));
+    // (the count through an empty asm: the compiler would keep the condition in
+    // a vector register, and spill it)
+    int nt = NT;
+    asm volatile("" : "+s"(nt));
+    return (uint32_t)__builtin_amdgcn_readfirstlane(nt <= WT_MAX_SORT ? s_ord[t] : tile_desc(t));
   };
   auto uni = [](uint64_t v) {
     return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
            (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
   };
 
-  // ---- load side ----
-  // Activations: half-step ca_h of step ca_k of item ca_n; this wavefront's
-  // 2 KB of it: row block 4 h + wave / 2, loads 2 (wave & 1) and + 1.  A row
-  // block of padding only is replaced by block 0 of the tile (loaded again,
-  // read by nobody).  Weights (and scales): step cw_k of item cw_n; piece wave
-  // of the eight.  Past the last item the last one is loaded again, so that
-  // every phase issues the same number of loads.
   const uint32_t ring_lds = lds_addr(ring);
   const uint32_t lane16 = lane * 16;
-  int ca_n = -1, ca_k = KT - 1, ca_h = 1, ca_u = WT_NA - 1;
-  int cw_n = -1, cw_k = KT - 1, cw_s = 1;
-  uint64_t a_base = 0, w_base = 0;
-  uint32_t a_blk[2] = {0, 0};
-  const char* s_ptr = nullptr;
-  uint32_t s_inc = 0;
-  auto load_a = [&]() {
-    if (++ca_u == WT_NA) ca_u = 0;
-    if ((ca_h ^= 1) == 0 && ++ca_k == KT) {
-      ca_k = 0;
-      ca_n = min(ca_n + 1, my_items - 1);
-      int nbt;
-      const uint32_t d = item_of(ca_n, nbt);
-      const int slot = d & 255, sub = d >> 8;
-      const int live = (min(WT_M, s_cnt[slot] - sub * WT_M) + 31) >> 5;
-      a_base = uni((uint64_t)(uintptr_t)p.A + (size_t)(s_st[slot] + sub) * KT * WT_STEP + (wave & 1) * 2048);
-#pragma unroll
-      for (int h = 0; h < 2; h++) {
-        const int b = 4 * h + (wave >> 1);
-        a_blk[h] = __builtin_amdgcn_readfirstlane(b < live ? b * 4096 : 0);
-      }
-    }
-    const char* src = reinterpret_cast<const char*>(a_base) + (size_t)ca_k * WT_STEP + (ca_h ? a_blk[1] : a_blk[0]);
-    const uint32_t dst = ring_lds + WT_A + ca_u * WT_UNIT + wave * 2048;
-    lds_dma16s(src, lane16, dst);
-    lds_dma16s(src, lane16 + 1024, dst + 1024);
+  struct Item {
+    int slot, sub, nbt, live;
   };
-  auto load_w = [&]() {
-    cw_s ^= 1;
-    if (++cw_k == KT) {
-      cw_k = 0;
-      cw_n = min(cw_n + 1, my_items - 1);
-      int nbt;
-      const uint32_t d = item_of(cw_n, nbt);
-      const int slot = d & 255, sub = d >> 8;
-      // (the second block of the last item of an odd number of blocks is the first again)
-      const int blk = min(2 * nbt + (wave >> 2), p.NB - 1);
-      w_base = uni((uint64_t)(uintptr_t)slot_tensor(p.W, p.w_slot_bytes, p.wtab, p.wfield, slot) +
-                   (size_t)blk * KT * B_BYTES + (wave & 3) * 4096);
-      if (F8) {
-        // lanes 0 .. 7: the scales of rows 32 wave .. 32 wave + 31; lanes 8, 9: those of the two weight blocks
-        const char* ws = slot_tensor(reinterpret_cast<const char*>(p.Wsp), p.ws_slot_floats * 4, p.wtab, p.sfield, slot);
-        const char* as = reinterpret_cast<const char*>(p.A_sc + ((size_t)(s_st[slot] + sub) * KT) * WT_M + 32 * wave);
-        s_ptr = lane < 8 ? as + lane16 : ws + (size_t)min(2 * nbt + (lane == 9 ? 1 : 0), p.NB - 1) * KT * 16;
-        s_inc = lane < 8 ? WT_M * 4 : 16;
-      }
-    }
-    const char* src = reinterpret_cast<const char*>(w_base) + (size_t)cw_k * B_BYTES;
-    const uint32_t dst = ring_lds + WT_W + cw_s * WT_STEP + wave * 4096;
-#pragma unroll
-    for (int j = 0; j < 4; j++) lds_dma16s(src, lane16 + j * 1024, dst + j * 1024);
-    if (F8) {
-      lds_dma16v_lanes(s_ptr, ring_lds + WT_S + cw_s * WT_SC + wave * WT_SCW, 0x3FFull);
-      s_ptr += s_inc;
-    }
+  auto item = [&](int n) {
+    Item it;
+    const uint32_t d = item_of(n, it.nbt);
+    it.slot = d & 255;
+    it.sub = d >> 8;
+    it.live = __builtin_amdgcn_readfirstlane(live_of(d));
+    return it;
   };
+  // this wavefront's weight piece of an item: piece wave of the eight (the
+  // second block of the last item of an odd number of blocks is the first again)
+  auto table = [&]() {
+    const uint64_t* t = p.wtab;  // (through an empty asm: see item_of)
+    asm volatile("" : "+s"(t));
+    return t;
+  };
+  auto w_of = [&](const Item& it) {
+    const int blk = min(2 * it.nbt + (wave >> 2), p.NB - 1);
+    return uni((uint64_t)(uintptr_t)slot_tensor(p.W, p.w_slot_bytes, table(), p.wfield, it.slot) +
+               (size_t)blk * KT * B_BYTES + (wave & 3) * 4096);
+  };
+  auto a_of = [&](const Item& it) {
+    return uni((uint64_t)(uintptr_t)p.A + (size_t)(s_st[it.slot] + it.sub) * KT * WT_STEP);
+  };
+  // fp8 scales of a step, one load: lanes 0 .. 7 those of rows 32 wave .. 32
+  // wave + 31, lanes 8 and 9 those of the two weight blocks
+  auto s_of = [&](const Item& it) {
+    const char* ws =
+        slot_tensor(reinterpret_cast<const char*>(p.Wsp), p.ws_slot_floats * 4, table(), p.sfield, it.slot);
+    const char* as =
+        reinterpret_cast<const char*>(p.A_sc + ((size_t)(s_st[it.slot] + it.sub) * KT) * WT_M + 32 * wave);
+    return lane < 8 ? as + lane16 : ws + (size_t)min(2 * it.nbt + (lane == 9 ? 1 : 0), p.NB - 1) * KT * 16;
+  };
+  const uint32_t s_inc = lane < 8 ? WT_M * 4 : 16;
+  constexpr uint64_t S_LANES = 0x3FFull;
 
-  // ---- compute side ----
+  // ---- compute ----
   f32x16 acc[4][2];
-  i32x8 fb[2][2];
-  int u_rd = 0, w_rd = 0;  // ring positions of the phase / step being read
+  i32x8 fa[2][2], fb[2][2];  // [buffer i % 2][half], [piece j][half]
   float sa[4], sw0 = 1.f, sw1 = 1.f;
   auto rd8 = [&](const char* s) {
     const i32x4 lo = *reinterpret_cast<const i32x4*>(s);
     const i32x4 hi = *reinterpret_cast<const i32x4*>(s + 1024);
     return (i32x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   };
-  const char* const my_a = ring + WT_A + wm * 4096 + lane16;
-  const char* const my_w = ring + WT_W + wn * 8192 + lane16;
-  const char* const my_s = ring + WT_S + wm * WT_SCW + (lane & 31) * 4;
-  auto read_w = [&]() {
-    const char* s = my_w + w_rd * WT_STEP;
+  // (the parts of this wavefront: w the weights of a step, a the rows of a half-step)
+  auto read_b = [&](const char* w, int j) {
+    const char* s = w + wn * 8192 + lane16 + j * 4096;
 #pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int h = 0; h < 2; h++) fb[j][h] = rd8(s + j * 4096 + h * 2048);
+    for (int h = 0; h < 2; h++) fb[j][h] = rd8(s + h * 2048);
   };
-  auto read_s = [&]() {
-    const char* s = my_s + w_rd * WT_SC;
+  auto read_s = [&](int slot) {
+    const char* s = ring + WT_S + slot * WT_SC + wm * WT_SCW + (lane & 31) * 4;
 #pragma unroll
     for (int i = 0; i < 4; i++) sa[i] = *reinterpret_cast<const float*>(s + 2 * i * WT_SCW);
-    const float2 v = *reinterpret_cast<const float2*>(ring + WT_S + w_rd * WT_SC + 128 + 16 * (wn >> 1));
+    const float2 v = *reinterpret_cast<const float2*>(ring + WT_S + slot * WT_SC + 128 + 16 * (wn >> 1));
     sw0 = v.x;
     sw1 = GATEUP ? v.y : v.x;
   };
-  auto read_a = [&](i32x8 (&a)[2], int i) {
-    const char* s = my_a + u_rd * WT_UNIT + 8192 * (i & 1);
+  auto read_a = [&](const char* a, int i) {
+    const char* s = a + wm * 4096 + lane16 + 8192 * (i & 1);
 #pragma unroll
-    for (int h = 0; h < 2; h++) a[h] = rd8(s + h * 2048);
+    for (int h = 0; h < 2; h++) fa[i & 1][h] = rd8(s + h * 2048);
   };
   auto ue = [](float s) { return (int)((__float_as_uint(s) >> 23) & 0xFF); };
-  // acc of row block i += its rows times this wavefront's weight rows, over one step
-  auto mul = [&](const i32x8 (&a)[2], int i) {
+  // acc of row block i += its rows times this wavefront's weight rows, over
+  // one step.  then(q) after a quarter of the MFMAs each: other instructions
+  // go between them one by one (a burst of loads from all wavefronts would
+  // queue in the texture addresser and hold up the MFMAs behind it).
+  auto mul = [&](int i, auto then) {
+    const i32x8(&a)[2] = fa[i & 1];
     if constexpr (DT == kWideBf16) {
 #pragma unroll
-      for (int ks = 0; ks < 4; ks++) {
-        const i32x8& av = a[ks >> 1];
-        const int o = 4 * (ks & 1);
-        const i32x4 ax = {av[o], av[o + 1], av[o + 2], av[o + 3]};
+      for (int j = 0; j < 2; j++) {
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
-          const i32x8& bv = fb[j][ks >> 1];
-          const i32x4 bx = {bv[o], bv[o + 1], bv[o + 2], bv[o + 3]};
+        for (int ks = 0; ks < 4; ks++) {
+          const int o = 4 * (ks & 1);
+          const i32x8 &av = a[ks >> 1], &bv = fb[j][ks >> 1];
+          const i32x4 ax = {av[o], av[o + 1], av[o + 2], av[o + 3]}, bx = {bv[o], bv[o + 1], bv[o + 2], bv[o + 3]};
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(reinterpret_cast<const bf16x8&>(bx),
                                                               reinterpret_cast<const bf16x8&>(ax), acc[i][j], 0, 0, 0);
+          if (ks & 1) {
+            __builtin_amdgcn_sched_barrier(0);
+            then(2 * j + (ks >> 1));
+          }
         }
       }
     } else if constexpr (MX) {
       const int ea = ue(sa[i]);
       const int eb = GATEUP ? ((lane & 16) ? ue(sw1) : ue(sw0)) : ue(sw0);
 #pragma unroll
-      for (int h = 0; h < 2; h++)
+      for (int j = 0; j < 2; j++) {
 #pragma unroll
-        for (int j = 0; j < 2; j++)
+        for (int h = 0; h < 2; h++) {
           acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][h], a[h], acc[i][j], 0, 0, 0, eb, 0, ea);
+          __builtin_amdgcn_sched_barrier(0);
+          then(2 * j + h);
+        }
+      }
     } else {
       f32x16 pp[2];
 #pragma unroll
       for (int j = 0; j < 2; j++) {
         const f32x16 z = {};
-        pp[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][0], a[0], z, 0, 0, 0, 127, 0, 127);
-        pp[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][1], a[1], pp[j], 0, 0, 0, 127, 0, 127);
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+          pp[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j][h], a[h], h ? pp[j] : z, 0, 0, 0, 127, 0, 127);
+          __builtin_amdgcn_sched_barrier(0);
+          then(2 * j + h);
+        }
       }
+      __builtin_amdgcn_sched_barrier(0);
       // elements 0 .. 7 belong to the gate rows of a piece, 8 .. 15 to the up rows
       const float s0 = sa[i] * sw0, s1 = sa[i] * sw1;
 #pragma unroll
@@ -416,76 +482,39 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
 #pragma unroll
         for (int e = 0; e < 16; e++) acc[i][j][e] += pp[j][e] * (e < 8 ? s0 : s1);
     }
-  };
-  // The end of a phase: what the next one reads has landed and every
-  // wavefront is done reading what the next one's loads overwrite.  Loads
-  // complete in order, and a wavefront issues 2 (activations) in the first
-  // phase of a step and 4 + SL + 2 in the second (weights and scales of step
-  // k + 2, then activations), each needed 3 issues later: the second half of
-  // step k at the end of its first phase, the weights and the first half of
-  // step k + 1 at the end of the second.  2 + (6 + SL) + 2 loads follow
-  // either.
-  auto phase_end = [&]() {
-    wait_lgkm0();
-    __builtin_amdgcn_s_waitcnt(TEMPO_VMCNT_IMM(IN_FLIGHT));
-    barrier_nofence();
     __builtin_amdgcn_sched_barrier(0);
-    if (++u_rd == WT_NA) u_rd = 0;
   };
+  auto nothing = [](int) {};
 
-  load_a();
-  load_w();
-  load_a();
-  load_a();
-  load_w();
-  load_a();
-  __builtin_amdgcn_s_waitcnt(TEMPO_VMCNT_IMM(IN_FLIGHT));
-  barrier_nofence();
-
-#pragma unroll 1
-  for (int n = 0; n < my_items; n++) {
-    int nbt;
-    const uint32_t d = item_of(n, nbt);
-    const int slot = d & 255, sub = d >> 8;
-    const int tile = __builtin_amdgcn_readfirstlane(s_st[slot] + sub);
-    const int row0 = __builtin_amdgcn_readfirstlane(s_off[slot] + sub * WT_M);
-    const int nvalid = __builtin_amdgcn_readfirstlane(min(WT_M, s_cnt[slot] - sub * WT_M));
+  // Start and end of an item: NI row blocks of this wavefront at most.
+  struct Out {
+    int n, nb;
+    uint64_t tstart;
+  };
+  auto begin = [&](auto ni, int n) {
+    constexpr int NI = decltype(ni)::value;
+    const Item it = item(n);
+    Out o;
+    o.n = n;
     // live row blocks 2 i + wm, i < nb, of this wavefront (none where its
     // weight block is past the last one)
-    const int nb = 2 * nbt + (wn >> 1) < p.NB ? (((nvalid + 31) >> 5) + 1 - wm) >> 1 : 0;
-    const uint64_t tstart = p.timing ? __builtin_amdgcn_s_memrealtime() : 0;
+    o.nb = 2 * it.nbt + (wn >> 1) < p.NB ? (it.live + 1 - wm) >> 1 : 0;
+    o.tstart = p.timing ? __builtin_amdgcn_s_memrealtime() : 0;
 #pragma unroll
-    for (int i = 0; i < 4; i++)
+    for (int i = 0; i < NI; i++)
 #pragma unroll
       for (int j = 0; j < 2; j++)
 #pragma unroll
         for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
-
-#pragma unroll 1
-    for (int k = 0; k < KT; k++) {
-#pragma unroll
-      for (int ph = 0; ph < 2; ph++) {
-        i32x8 a0[2], a1[2];
-        read_a(a0, 2 * ph);
-        if (ph == 0) {
-          read_w();
-          if (F8) read_s();
-        }
-        read_a(a1, 2 * ph + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (ph == 1) {
-          load_w();
-          w_rd ^= 1;
-        }
-        load_a();
-        __builtin_amdgcn_sched_barrier(0);
-        if (2 * ph < nb) mul(a0, 2 * ph);
-        if (2 * ph + 1 < nb) mul(a1, 2 * ph + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        phase_end();
-      }
-    }
-
+    return o;
+  };
+  auto finish = [&](auto ni, const Out& o) {
+    constexpr int NI = decltype(ni)::value;
+    const Item it = item(o.n);
+    const int nbt = it.nbt, nb = o.nb;
+    const int tile = __builtin_amdgcn_readfirstlane(s_st[it.slot] + it.sub);
+    const int row0 = __builtin_amdgcn_readfirstlane(s_off[it.slot] + it.sub * WT_M);
+    const int nvalid = __builtin_amdgcn_readfirstlane(min(WT_M, s_cnt[it.slot] - it.sub * WT_M));
     // Epilogue.  Lane l of tile (i, j) holds token row 32 (2 i + wm) + l % 32
     // and, in element e, packed weight row 8 (e / 4) + 4 (l / 32) + e % 4 of
     // piece 2 (wn & 1) + j of block 2 nbt + wn / 2 (gate/up: rows 0 .. 15
@@ -510,7 +539,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
       // h in place of the gate elements, and its amax over the item's 128
       // columns: this lane's, the row's other lane's, the other wavefronts'
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
+      for (int i = 0; i < NI; i++) {
         float m = 0.f;
 #pragma unroll
         for (int j = 0; j < 2; j++)
@@ -531,7 +560,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
                  (32 * (wn & 1) + l31) * 16;
       float* hs = p.C_sc + ((size_t)tile * (p.NB / 2) + nbt) * WT_M;
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
+      for (int i = 0; i < NI; i++) {
         if (i >= nb) continue;
         const int r = 32 * (2 * i + wm) + l31;
         const float mm = fmaxf(fmaxf(xamax[0][r], xamax[1][r]), fmaxf(xamax[2][r], xamax[3][r]));
@@ -542,12 +571,21 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
           sc = __uint_as_float(bits);
         }
         if (wn == 0 && hl == 0) hs[r] = sc;
+        // h / sc, correctly rounded from the reciprocal (Markstein 1990: r =
+        // 1 / sc, q0 = h r, q = q0 + (h - q0 sc) r); tiny rows are scaled up
+        // so that r stays finite, and an infinite sc gives 0 or NaN like the
+        // division
+        const float up = mm < 1e-20f ? 0x1p64f : 1.0f;
+        const float scs = __builtin_isinf(sc) ? 0.f : sc * up, rcp = __builtin_isinf(sc) ? 0.f : 1.0f / scs;
         uint32_t w[2][2];
 #pragma unroll
         for (int j = 0; j < 2; j++) {
           float q[8];
 #pragma unroll
-          for (int e = 0; e < 8; e++) q[e] = fminf(fmaxf(acc[i][j][e] / sc, -448.f), 448.f);
+          for (int e = 0; e < 8; e++) {
+            const float v = acc[i][j][e] * up, q0 = v * rcp;
+            q[e] = fminf(fmaxf(fmaf(fmaf(-q0, scs, v), rcp, q0), -448.f), 448.f);
+          }
 #pragma unroll
           for (int t = 0; t < 2; t++) {
             uint32_t v = __builtin_amdgcn_cvt_pk_fp8_f32(q[4 * t], q[4 * t + 1], 0, false);
@@ -566,7 +604,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
       // load p, lane l % 32 + 32 q
       char* hb = p.C + ((size_t)tile * p.NB + 2 * nbt + (wn >> 1)) * WT_STEP + 2 * (wn & 1) * 1024 + lid * 16;
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
+      for (int i = 0; i < NI; i++) {
         if (i >= nb) continue;
 #pragma unroll
         for (int j = 0; j < 2; j++) {
@@ -582,7 +620,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     } else {
       char* yb = p.C + (size_t)row0 * p.ld_out + (size_t)(256 * nbt + 64 * wn + 8 * hl) * 2;
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
+      for (int i = 0; i < NI; i++) {
         if (i >= nb) continue;
         const int r = 32 * (2 * i + wm) + l31;
         char* yr = yb + (size_t)r * p.ld_out;
@@ -602,12 +640,268 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     }
     if (p.timing && tid == 0) {
       const uint64_t tend = __builtin_amdgcn_s_memrealtime();
-      atomicMin(reinterpret_cast<unsigned long long*>(&p.t0[slot]), (unsigned long long)tstart);
-      atomicMax(reinterpret_cast<unsigned long long*>(&p.t1[slot]), (unsigned long long)tend);
+      atomicMin(reinterpret_cast<unsigned long long*>(&p.t0[it.slot]), (unsigned long long)o.tstart);
+      atomicMax(reinterpret_cast<unsigned long long*>(&p.t1[it.slot]), (unsigned long long)tend);
     }
+  };
+  // Everyone's reads are done and at most n of this wavefront's loads are in flight.
+  auto sync = [&](auto nc) {
+    wait_lgkm0();
+    __builtin_amdgcn_s_waitcnt(TEMPO_VMCNT_IMM(decltype(nc)::value));
+    barrier_nofence();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // ---- items n0 .. n1 - 1, tiles of more than four live row blocks ----
+  // Two slots of weights, five half-steps of activations.  Fragments are read
+  // one row block ahead: while the MFMAs of row block i run, those of i + 1
+  // come out of LDS, and the first row block and weight piece of the next step
+  // during the last row block of this one.  Past the last item the last one is
+  // loaded again, so that every barrier sees the same number of loads; a row
+  // block of padding only is replaced by block 0 of the tile (read by nobody).
+  auto run_wide = [&](int n0, int n1) {
+    int ca_n = n0 - 1, ca_k = KT - 1, ca_h = 1, ca_u = WT_NA - 1;
+    int cw_n = n0 - 1, cw_k = KT - 1, cw_s = 1;
+    uint64_t a_base = 0, w_base = 0;
+    uint32_t a_blk[2] = {0, 0};
+    const char* s_ptr = nullptr;
+    // a half-step: this wavefront's 2 KB of it (row block 4 h + wave / 2, loads 2 (wave & 1) and + 1)
+    uint64_t a_src = 0, w_src = 0;
+    uint32_t a_dst = 0, w_dst = 0, s_dst = 0;
+    auto next_a = [&]() {
+      if (++ca_u == WT_NA) ca_u = 0;
+      if ((ca_h ^= 1) == 0 && ++ca_k == KT) {
+        ca_k = 0;
+        ca_n = min(ca_n + 1, n1 - 1);
+        const Item it = item(ca_n);
+        a_base = a_of(it) + (wave & 1) * 2048;
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+          const int b = 4 * h + (wave >> 1);
+          a_blk[h] = __builtin_amdgcn_readfirstlane(b < it.live ? b * 4096 : 0);
+        }
+      }
+      a_src = a_base + (size_t)ca_k * WT_STEP + (ca_h ? a_blk[1] : a_blk[0]);
+      a_dst = ring_lds + WT_A + ca_u * WT_UNIT + wave * 2048;
+    };
+    auto next_w = [&]() {
+      cw_s ^= 1;
+      if (++cw_k == KT) {
+        cw_k = 0;
+        cw_n = min(cw_n + 1, n1 - 1);
+        const Item it = item(cw_n);
+        w_base = w_of(it);
+        if (F8) s_ptr = s_of(it);
+      }
+      w_src = w_base + (size_t)cw_k * B_BYTES;
+      w_dst = ring_lds + WT_W + cw_s * WT_STEP + wave * 4096;
+      s_dst = ring_lds + WT_S + cw_s * WT_SC + wave * WT_SCW;
+    };
+    auto load_s = [&]() {
+      if (F8) {
+        lds_dma16v_lanes(s_ptr, s_dst, S_LANES);
+        s_ptr += s_inc;
+      }
+    };
+    auto load_a = [&]() {
+      next_a();
+      lds_dma16s_x2(a_src, lane16, a_dst);
+    };
+    auto load_w = [&]() {
+      next_w();
+      lds_dma16s_x4(w_src, lane16, w_dst);
+      load_s();
+    };
+    // the same, one load after a quarter of a row block's MFMAs each
+    auto put_w = [&](int q) {
+      if (q == 0) lds_dma16s_at<0>(w_src, lane16, w_dst);
+      if (q == 1) lds_dma16s_at<1>(w_src, lane16, w_dst);
+      if (q == 2) lds_dma16s_at<2>(w_src, lane16, w_dst);
+      if (q == 3) lds_dma16s_at<3>(w_src, lane16, w_dst);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto put_sa = [&](int q) {
+      if (q == 0) load_s();
+      if (q == 1) lds_dma16s_at<0>(a_src, lane16, a_dst);
+      if (q == 2) lds_dma16s_at<1>(a_src, lane16, a_dst);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto all = [&](auto put) {
+#pragma unroll
+      for (int q = 0; q < 4; q++) put(q);
+    };
+    // The two barriers of a step, each one row block ahead of the reads that
+    // need it: the second half-step's rows have landed (after row block 0),
+    // the next step's weights, scales and first half-step have (after row
+    // block 2); and every wavefront is done with what the loads issued next
+    // overwrite: the weights of this step and the second half-step of the one
+    // before, then the first half-step of this one.  Loads complete in order;
+    // 4 + SL + 2 are issued after the first barrier (weights and scales of
+    // step k + 2, its first half-step), 2 after the second (its second
+    // half-step), each is needed three barriers later, and one of each
+    // follow it.
+    constexpr std::integral_constant<int, 8 + SL> in_flight{};
+    auto unit_at = [](int u) { return u >= WT_NA ? u - WT_NA : u; };
+    int u_rd = 0, w_rd = 0;  // ring positions of the step: its first half-step, its weights
+    auto a_at = [&](int u) { return ring + WT_A + u * WT_UNIT; };
+    auto w_at = [&](int s) { return ring + WT_W + s * WT_STEP; };
+    load_w();
+    load_a();
+    load_a();
+    load_w();
+    load_a();
+    load_a();
+    sync(std::integral_constant<int, 10 + SL>{});
+    read_a(a_at(0), 0);
+    read_b(w_at(0), 0);
+    if (MX) read_s(0);
+#pragma unroll 1
+    for (int n = n0; n < n1; n++) {
+      const Out o = begin(std::integral_constant<int, 4>{}, n);
+      const int nb = o.nb;
+#pragma unroll 1
+      for (int k = 0; k < KT; k++) {
+        read_b(w_at(w_rd), 1);
+        read_a(a_at(u_rd), 1);
+        if (F8 && !MX) read_s(w_rd);
+        __builtin_amdgcn_sched_barrier(0);
+        if (0 < nb) mul(0, nothing);
+        sync(in_flight);
+        next_w();
+        next_a();
+        w_rd ^= 1;
+        u_rd = unit_at(u_rd + 1);
+        read_a(a_at(u_rd), 2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (1 < nb) mul(1, put_w);
+        else all(put_w);
+        read_a(a_at(u_rd), 3);
+        __builtin_amdgcn_sched_barrier(0);
+        if (2 < nb) mul(2, put_sa);
+        else all(put_sa);
+        sync(in_flight);
+        next_a();
+        u_rd = unit_at(u_rd + 1);
+        read_a(a_at(u_rd), 0);
+        __builtin_amdgcn_sched_barrier(0);
+        auto put_ab = [&](int q) {
+          if (q == 0) lds_dma16s_at<0>(a_src, lane16, a_dst);
+          if (q == 1) read_b(w_at(w_rd), 0);  // (its registers are free: the first piece's MFMAs have been issued)
+          if (q == 2) lds_dma16s_at<1>(a_src, lane16, a_dst);
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        if (3 < nb) mul(3, put_ab);
+        else all(put_ab);
+        if (MX) read_s(w_rd);
+      }
+      finish(std::integral_constant<int, 4>{}, o);
+    }
+  };
+
+  // ---- items n0 .. n1 - 1, tiles of at most four live row blocks ----
+  // These wait for their weights, so the ring holds whole steps instead, of
+  // the weights and up to ab row blocks: three of 48 KB, or four of 36 KB for
+  // tiles of one live row block.
+  auto run_narrow = [&](int n0, int n1, auto nslc) {
+    constexpr int NSL = decltype(nslc)::value;
+    constexpr int AB = NSL == 4 ? 4096 : WT_UNIT, SLOT = WT_STEP + AB;
+    static_assert(NSL * SLOT <= WT_S, "the ring holds the slots");
+    constexpr int L = 6 + SL;  // loads of a step
+    int c_n = n0 - 1, c_k = KT - 1, c_s = NSL - 1;
+    uint64_t a_base = 0, w_base = 0;
+    int a_b = 0;  // 1 where this wavefront's row block is live
+    const char* s_ptr = nullptr;
+    uint64_t a_src = 0, w_src = 0;
+    uint32_t dst = 0, s_dst = 0;
+    auto next = [&]() {
+      if (++c_s == NSL) c_s = 0;
+      if (++c_k == KT) {
+        c_k = 0;
+        c_n = min(c_n + 1, n1 - 1);
+        const Item it = item(c_n);
+        w_base = w_of(it);
+        a_base = a_of(it) + wave * 2048;
+        a_b = __builtin_amdgcn_readfirstlane((wave >> 1) < it.live ? 1 : 0);
+        if (F8) s_ptr = s_of(it);
+      }
+      dst = ring_lds + c_s * SLOT;
+      s_dst = ring_lds + WT_S + c_s * WT_SC + wave * WT_SCW;
+      w_src = w_base + (size_t)c_k * B_BYTES;
+      a_src = a_base + (size_t)c_k * WT_STEP;
+    };
+    auto put_w = [&](int q) {
+      if (q == 0) lds_dma16s_at<0>(w_src, lane16, dst + AB + wave * 4096);
+      if (q == 1) lds_dma16s_at<1>(w_src, lane16, dst + AB + wave * 4096);
+      if (q == 2) lds_dma16s_at<2>(w_src, lane16, dst + AB + wave * 4096);
+      if (q == 3) lds_dma16s_at<3>(w_src, lane16, dst + AB + wave * 4096);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto put_sa = [&](int q) {
+      if (F8 && q == 0) {
+        lds_dma16v_lanes(s_ptr, s_dst, S_LANES);
+        s_ptr += s_inc;
+      }
+      if (q == 1) lds_dma16s_x2_if(a_src, lane16, dst + wave * 2048, a_b);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto all = [&](auto put) {
+#pragma unroll
+      for (int q = 0; q < 4; q++) put(q);
+    };
+    constexpr std::integral_constant<int, (NSL - 2) * L> in_flight{};
+#pragma unroll
+    for (int i = 0; i < NSL - 1; i++) {
+      next();
+      all(put_w);
+      all(put_sa);
+    }
+    sync(in_flight);
+    int rd = 0;
+#pragma unroll 1
+    for (int n = n0; n < n1; n++) {
+      const Out o = begin(std::integral_constant<int, 2>{}, n);
+      const int nb = o.nb;
+#pragma unroll 1
+      for (int k = 0; k < KT; k++) {
+        const char* st = ring + rd * SLOT;
+        if (0 < nb) {
+          read_b(st + AB, 0);
+          read_a(st, 0);
+          read_b(st + AB, 1);
+          if (F8) read_s(rd);
+          if (1 < nb) read_a(st, 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        next();
+        if (0 < nb) mul(0, put_w);
+        else all(put_w);
+        if (1 < nb) mul(1, put_sa);
+        else all(put_sa);
+        // step k + 1 has landed and everyone is done with this one's slot
+        sync(in_flight);
+        if (++rd == NSL) rd = 0;
+      }
+      finish(std::integral_constant<int, 2>{}, o);
+    }
+  };
+
+  // the items in runs of one kind (at most three, as the order is sorted)
+  auto kind = [&](int n) {
+    const int live = sorted ? item(n).live : 8;
+    return live > 4 ? 0 : live > 1 ? 1 : 2;
+  };
+#pragma unroll 1
+  for (int n0 = 0; n0 < my_items;) {
+    const int kd = kind(n0);
+    int n1 = n0 + 1;
+    while (n1 < my_items && kind(n1) == kd) n1++;
+    if (kd == 0) run_wide(n0, n1);
+    else if (kd == 1) run_narrow(n0, n1, std::integral_constant<int, 3>{});
+    else run_narrow(n0, n1, std::integral_constant<int, 4>{});
+    n0 = n1;
+    // no DMA of one run may land in the next one's ring, or outlive the workgroup
+    sync(std::integral_constant<int, 0>{});
   }
-  // no DMA into this workgroup's LDS may outlive it
-  __builtin_amdgcn_s_waitcnt(TEMPO_VMCNT_IMM(0));
 }
 
 template <int DT>
@@ -679,27 +973,29 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 // Where the wide tiles win: slots with enough rows, and enough items to fill
 // the chip.  The counts per slot are only known on the device; rows per
 // expert, T K / E, and the items that these make, stand for them (the same
-// for every plan and, but for the 256-row kernels, every M-tile, so a row's
-// result depends on neither).
-// Measured, forward us, other kernel -> wide tiles (18 or 36 slots, H 4096 /
-// 7168, uniform plan):
-//   fp8    16 rows per expert 128 -> 132, 32: 150 -> 146, 64: 181 -> 154,
-//          128: 254 -> 189, 256: 408 -> 255, 512 (18 slots): 713 -> 389;
-//          items 110: 94 -> 104, 139: 101 -> 100, 155: 91 -> 83,
-//          225: 153 -> 112
-//   UE8M0  32: 145 -> 139, 28 (36 slots): 327 -> 329, 64: 163 -> 146; its own
-//          256-row kernel, where that runs, is faster (320 -> 362 at 512)
-//   bf16   36: 213 -> 214, 65 (36 slots, M 128): 654 -> 690, 92: 304 -> 256,
-//          160: 324 -> 271, 265: 393 -> 368, 405: 495 -> 480, 512: 556 -> 567;
-//          items 156: 114 -> 131
+// for every plan, so a row's result does not depend on it).
+// Measured, forward us, other kernel -> wide tiles (uniform plans; 18 slots H
+// 4096 I 1536 unless 36 slots H 7168 I 2048 or 10 slots H 2048 I 1408 is said):
+//   fp8    rows per expert 8: 103 -> 100 (36 slots 323 -> 326), 16: 129 -> 112
+//          (36 slots 389 -> 380), 32: 149 -> 127, 64: 181 -> 137, 128: 252 ->
+//          164, 512: 710 -> 368; items 30: 78 -> 95, 67: 102 -> 101, 114: 71
+//          -> 72, 139: 100 -> 87
+//   UE8M0  16: 119 -> 112 (36 slots 371 -> 376), 32: 142 -> 125 (36 slots 488
+//          -> 408), 64: 164 -> 133, 128: 219 -> 164; short contractions
+//          (H 1152): 32: 68 -> 72, 96: 81 -> 74; items 73: 94 -> 91; against its
+//          own 256-row kernel 160: 173 -> 173, 512: 327 -> 333
+//   bf16   16: 178 -> 179, 32: 208 -> 202 (36 slots 854 -> 735), 64: 249 ->
+//          208 (36 slots with 128-row tiles 651 -> 669), 92: 305 -> 228, 187:
+//          316 -> 247, 512: 593 -> 551; items 133: 175 -> 191, 192 (10 slots):
+//          126 -> 138, 275 (10 slots): 160 -> 153
 bool experts_wide_wanted(const tempo_moe_shape& s) {
   if (experts_big_f8_supported(s)) return false;
-  const long long P = (long long)s.T * s.K;
+  const long long P = (long long)s.T * s.K, E = s.E;
   // items of the gate/up GEMM, were the pairs spread evenly over the experts
-  const long long items = (s.S + P * s.S / (256ll * s.E)) * (s.I / 128);
-  if (s.dtype == TEMPO_BF16)
-    return P >= 80ll * s.E && items >= 200 && (P < 384ll * s.E || !experts_big_supported(s));
-  return P >= (s.dtype == TEMPO_FP8_E4M3 ? 32ll : 48ll) * s.E && items >= 150;
+  const long long items = (s.S + P * s.S / (256 * E)) * (s.I / 128);
+  if (s.dtype == TEMPO_BF16) return items >= 200 && P >= (s.m_tile == 64 ? 32 : 80) * E;
+  if (s.dtype == TEMPO_FP8_E4M3) return items >= 80 && P >= 12 * E;
+  return items >= 80 && P >= (s.H >= 2048 ? 24 : 64) * E;
 }
 
 hipError_t launch_experts_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,
