@@ -14,34 +14,6 @@ namespace tempo {
 
 static size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// The wide-tile kernels' buffers.  They run in place of the kernels that use
-// the regions from h on, so they lie over those: h next to the packed
-// activations, which are dead once the gate/up GEMM is done, and only these
-// may share y_perm's bytes (the down GEMM reads h while it writes y_perm).  A
-// workspace grows for them only where it is past the static scratch array
-// or fits it all the same; otherwise the shape keeps the other kernels.
-static void place_wide(const tempo_moe_shape& s, Layout& L) {
-  const size_t es = s.dtype == TEMPO_BF16 ? 2 : 1;
-  // a slot's last tile is the only partly filled one
-  const size_t tiles = (size_t)s.T * s.K / 256 + s.S;
-  const size_t a = align_up(tiles * 256 * s.H * es), a_sc = es == 1 ? align_up(tiles * (s.H / 128) * 1024) : 0;
-  const size_t h = align_up(tiles * 256 * s.I * es), h_sc = es == 1 ? align_up(tiles * (s.I / 128) * 1024) : 0;
-  if (h + h_sc <= L.y_perm - L.h && a + a_sc <= L.total - L.y_perm) {
-    L.wide_h = L.h;
-    L.wide_a = L.y_perm;
-  } else {
-    L.wide_h = L.apack;  // past y_perm
-    L.wide_a = a + a_sc <= L.apack - L.h ? L.h : L.wide_h + h + h_sc;
-    const size_t end = std::max(L.wide_a + a + a_sc, L.wide_h + h + h_sc);
-    // (a shape that fitted the static scratch array still does)
-    if (end > L.total && end > (size_t)TEMPO_STATIC_SCRATCH_BYTES && L.total <= (size_t)TEMPO_STATIC_SCRATCH_BYTES) return;
-    L.total = std::max(L.total, end);
-  }
-  L.wide_a_sc = L.wide_a + a;
-  L.wide_h_sc = L.wide_h + h;
-  L.wide_tiles = (int)tiles;
-}
-
 Layout make_layout(const tempo_moe_shape& s) {
   Layout L{};
   const size_t P = (size_t)s.T * s.K;
@@ -83,7 +55,19 @@ Layout make_layout(const tempo_moe_shape& s) {
   L.fix = o;  // per workgroup: the split work item it completes (12 int32)
   o = align_up(o + (size_t)persistent_grid(1) * 12 * 4);
   L.total = o;
-  if (experts_wide_wanted(s)) place_wide(s, L);
+  if (experts_wide_wanted(s)) {
+    // The wide-tile kernels' buffers lie over those of the kernels they run in
+    // place of: packed h (as large as row_cap rows of h) and its scales over
+    // h, the packed activations and their scales over y_perm, which is written
+    // by the down GEMM, when they are dead (fp8: H bytes and H / 32 of scales a
+    // row, under the 2 H of a bf16 row).
+    L.wide_h = L.h;
+    L.wide_h_sc = L.h_scale;
+    L.wide_a = L.y_perm;
+    L.wide_a_sc = L.y_perm + (size_t)L.row_cap * s.H;  // (fp8)
+    // a slot's last tile is the only partly filled one
+    L.wide_tiles = (int)(P / 256 + s.S);
+  }
   return L;
 }
 

@@ -7,11 +7,14 @@
 //   sets the padding between slots.
 // * Operands in MFMA operand order: the weights from tempo_moe_pack_weights,
 //   the activation rows of every wide tile from k_pack_wide, and h from the
-//   gate/up epilogue.  Per 128-byte contraction step a packed tile is 32 KB;
-//   rows 32b .. 32b + 31 form the 4 KB piece b, four 1 KB loads j in which
-//   lane l holds 16-byte chunk c(j, l) of row 32b + l % 32 (fp8
+//   gate/up epilogue.  Per 128-byte contraction step a packed tile is 4 KB per
+//   live block of 32 rows; rows 32b .. 32b + 31 form piece b, four 1 KB loads j
+//   in which lane l holds 16-byte chunk c(j, l) of row 32b + l % 32 (fp8
 //   c = 4 (j / 2) + 2 (l / 32) + j % 2, bf16 c = 2 j + l / 32), like the packed
-//   weights.  fp8 activation scales go beside it as 256 fp32 per tile and step.
+//   weights.  A tile starts where its first row's offset puts it (offsets are
+//   multiples of the M-tile, so of 32), so that packed rows take no more room
+//   than padded ones.  fp8 activation scales lie alike, 32 fp32 per live block
+//   and step.
 // * Eight wavefronts, two per SIMD: wavefront (wm, wn) takes the row blocks
 //   2 i + wm (i = 0 .. 3) against the weight rows 64 wn .. 64 wn + 63 (two
 //   pieces j), 128 accumulator registers per lane.  With fp32 block scales a
@@ -62,14 +65,14 @@ constexpr int WT_A = 0;                      // LDS ring: activations,
 constexpr int WT_W = WT_NA * WT_UNIT;        //   weights (2 slots),
 constexpr int WT_S = WT_W + 2 * WT_STEP;     //   scales (up to 4 slots)
 constexpr int WT_RING = WT_S + 4 * WT_SC;
-constexpr int WT_MAX_SORT = 1024;            // tiles the cost-ordered list covers (beyond: tile order)
+constexpr int WT_MAX_SORT = 768;             // tiles the cost-ordered list covers (beyond: tile order)
 constexpr int WT_GM = 4;                     // tiles per group of the item order
 
 enum WideType : int { kWideF8 = 0, kWideMX = 1, kWideBf16 = 2 };
 
 struct WideArgs {
   const char* A;          // packed activation tiles
-  const float* A_sc;      // fp8: [tile][step][256]
+  const float* A_sc;      // fp8: their scales
   const char* W;          // packed weights
   size_t w_slot_bytes;
   const float* Wsp;       // fp8: packed weight scales [slot][block][step][4]
@@ -77,7 +80,7 @@ struct WideArgs {
   const uint64_t* wtab;
   int wfield, sfield;
   char* C;                // gate/up: packed h tiles; down: y_perm rows (bf16)
-  float* C_sc;            // gate/up, fp8: h scales [tile][step][256]
+  float* C_sc;            // gate/up, fp8: their scales
   const int32_t* slot_counts;
   const int32_t* slot_offsets;
   int S, KT, NB, max_tiles;  // KT: steps per item; NB: 128-row weight blocks
@@ -132,14 +135,20 @@ __device__ __forceinline__ int wide_slot(const int32_t* st, int S, int t) {
   return lo;
 }
 
+// The first piece (32 rows) of rows from offset off + 256 sub on.
+__device__ __forceinline__ size_t wide_piece(int off, int sub) { return (size_t)(off >> 5) + 8 * sub; }
+
 // The activation rows of every wide tile in packed order, from token rows
 // (gather: row r is token row_token[r] of A) or from permuted rows; fp8
 // scales from the token rows' own [token][KT] (gather) or the block-major
 // [KT][row_cap] ones of stage 1.  Padding rows of a live row block are zero
-// with scale 1; row blocks of padding only are not written.  One (tile, step)
-// block of 32 KB per workgroup of a fixed grid at a time.  x_perm, x_perm_sc
+// with scale 1; row blocks of padding only are not written.  x_perm, x_perm_sc
 // (each nullable): the stage-1 outputs of the same rows, which the forward
-// leaves to this kernel.
+// leaves to this kernel.  One (tile, step) block per workgroup of a fixed grid
+// at a time, through LDS, so that 8 lanes read (and write to x_perm) the 128
+// consecutive bytes of a row and 64 lanes write 1 KB: fp8 prefill share with
+// x_perm 45 us when every lane read and wrote its own 16 bytes of a row, 39
+// like this.
 template <bool FP8>
 __global__ __launch_bounds__(256) void k_pack_wide(const char* __restrict__ A, const float* __restrict__ A_scale,
                                                    int gather, int row_cap, const int32_t* __restrict__ row_token,
@@ -148,61 +157,59 @@ __global__ __launch_bounds__(256) void k_pack_wide(const char* __restrict__ A, c
                                                    int KT, char* __restrict__ out, float* __restrict__ out_sc,
                                                    char* __restrict__ x_perm, float* __restrict__ x_perm_sc) {
   __shared__ int32_t s_cnt[kMaxS], s_off[kMaxS], s_st[kMaxS + 1];
+  __shared__ __attribute__((aligned(16))) char stage[WT_STEP];  // rows of 128 bytes, chunk c at c ^ (row % 8)
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   wide_slots(slot_counts, slot_offsets, S, row_cap, s_off, s_cnt, tid, 256);
   __syncthreads();
   if (tid < 64) wide_prefix(s_cnt, s_st, S);
   __syncthreads();
   const int blocks = min(s_st[S], max_tiles) * KT;
+  const size_t row_bytes = (size_t)KT * 128;
 #pragma unroll 1
   for (int blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
     const int tile = blk / KT, kt = blk - tile * KT;
     const int slot = __builtin_amdgcn_readfirstlane(wide_slot(s_st, S, tile));
-    const int sub = (tile - s_st[slot]) * WT_M;
-    const int row0 = s_off[slot] + sub, nvalid = min(WT_M, s_cnt[slot] - sub);
-    int tok[2];
+    const int sub = tile - s_st[slot];
+    const int row0 = s_off[slot] + sub * WT_M, nvalid = min(WT_M, s_cnt[slot] - sub * WT_M);
+    const int live = (nvalid + 31) >> 5;
+    const size_t piece = wide_piece(s_off[slot], sub) * KT + (size_t)kt * live;
+    int src[8];
+    i32x4 v[8];
 #pragma unroll
-    for (int pb = 0; pb < 2; pb++) {
-      const int r = 32 * (2 * w + pb) + (lane & 31);
-      tok[pb] = r < nvalid ? (gather ? row_token[row0 + r] : row0 + r) : -1;
-    }
-    i32x4 v[2][4];
-#pragma unroll
-    for (int pb = 0; pb < 2; pb++) {
-      if (32 * (2 * w + pb) >= nvalid) continue;
-      const size_t src = (size_t)max(tok[pb], 0) * KT * 128 + kt * 128;
-#pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const int c = FP8 ? 4 * (j >> 1) + 2 * (lane >> 5) + (j & 1) : 2 * j + (lane >> 5);
-        v[pb][j] = *reinterpret_cast<const i32x4*>(A + src + c * 16);
-      }
+    for (int i = 0; i < 8; i++) {
+      const int r = 32 * i + (tid >> 3);
+      src[i] = r < nvalid ? (gather ? max(row_token[row0 + r], 0) : row0 + r) : -1;
     }
     float sc = 1.f;
     if (FP8 && tid < nvalid) {
       if (gather) sc = A_scale[(size_t)max(row_token[row0 + tid], 0) * KT + kt];
       else sc = A_scale[(size_t)kt * row_cap + row0 + tid];
     }
-    char* dst = out + (size_t)blk * WT_STEP;
 #pragma unroll
-    for (int pb = 0; pb < 2; pb++) {
-      const int b = 2 * w + pb;
-      if (32 * b >= nvalid) continue;
+    for (int i = 0; i < 8; i++) {
+      v[i] = (i32x4){0, 0, 0, 0};
+      if (src[i] >= 0)
+        v[i] = *reinterpret_cast<const i32x4*>(A + (size_t)src[i] * row_bytes + kt * 128 + (tid & 7) * 16);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      if (i >= live) break;
+      const int r = 32 * i + (tid >> 3);
+      *reinterpret_cast<i32x4*>(stage + swz(r, tid & 7)) = v[i];
+      if (x_perm && src[i] >= 0)
+        *reinterpret_cast<i32x4*>(x_perm + (size_t)(row0 + r) * row_bytes + kt * 128 + (tid & 7) * 16) = v[i];
+    }
+    if (FP8 && tid < 32 * live) out_sc[piece * 32 + tid] = sc;
+    if (FP8 && x_perm_sc && tid < nvalid) x_perm_sc[(size_t)kt * row_cap + row0 + tid] = sc;
+    __syncthreads();
+    for (int b = w; b < live; b += 4)
 #pragma unroll
       for (int j = 0; j < 4; j++) {
-        const i32x4 z = {0, 0, 0, 0};
-        *reinterpret_cast<i32x4*>(dst + b * 4096 + j * 1024 + lane * 16) = tok[pb] < 0 ? z : v[pb][j];
+        const int c = FP8 ? 4 * (j >> 1) + 2 * (lane >> 5) + (j & 1) : 2 * j + (lane >> 5);
+        *reinterpret_cast<i32x4*>(out + (piece + b) * 4096 + j * 1024 + lane * 16) =
+            *reinterpret_cast<const i32x4*>(stage + swz(32 * b + (lane & 31), c));
       }
-      if (x_perm && tok[pb] >= 0) {
-        char* xr = x_perm + (size_t)(row0 + 32 * b + (lane & 31)) * KT * 128 + kt * 128;
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-          const int c = FP8 ? 4 * (j >> 1) + 2 * (lane >> 5) + (j & 1) : 2 * j + (lane >> 5);
-          *reinterpret_cast<i32x4*>(xr + c * 16) = v[pb][j];
-        }
-      }
-    }
-    if (FP8) out_sc[(size_t)blk * WT_M + tid] = sc;
-    if (FP8 && x_perm_sc && tid < nvalid) x_perm_sc[(size_t)kt * row_cap + row0 + tid] = sc;
+    __syncthreads();
   }
 }
 
@@ -385,18 +392,18 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
                (size_t)blk * KT * B_BYTES + (wave & 3) * 4096);
   };
   auto a_of = [&](const Item& it) {
-    return uni((uint64_t)(uintptr_t)p.A + (size_t)(s_st[it.slot] + it.sub) * KT * WT_STEP);
+    return uni((uint64_t)(uintptr_t)p.A + wide_piece(s_off[it.slot], it.sub) * KT * 4096);
   };
   // fp8 scales of a step, one load: lanes 0 .. 7 those of rows 32 wave .. 32
-  // wave + 31, lanes 8 and 9 those of the two weight blocks
+  // wave + 31 (of the last live block for the dead ones), lanes 8 and 9 those
+  // of the two weight blocks
   auto s_of = [&](const Item& it) {
     const char* ws =
         slot_tensor(reinterpret_cast<const char*>(p.Wsp), p.ws_slot_floats * 4, table(), p.sfield, it.slot);
     const char* as =
-        reinterpret_cast<const char*>(p.A_sc + ((size_t)(s_st[it.slot] + it.sub) * KT) * WT_M + 32 * wave);
+        reinterpret_cast<const char*>(p.A_sc + (wide_piece(s_off[it.slot], it.sub) * KT + min(wave, it.live - 1)) * 32);
     return lane < 8 ? as + lane16 : ws + (size_t)min(2 * it.nbt + (lane == 9 ? 1 : 0), p.NB - 1) * KT * 16;
   };
-  const uint32_t s_inc = lane < 8 ? WT_M * 4 : 16;
   constexpr uint64_t S_LANES = 0x3FFull;
 
   // ---- compute ----
@@ -512,7 +519,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     constexpr int NI = decltype(ni)::value;
     const Item it = item(o.n);
     const int nbt = it.nbt, nb = o.nb;
-    const int tile = __builtin_amdgcn_readfirstlane(s_st[it.slot] + it.sub);
+    const size_t piece = wide_piece(s_off[it.slot], it.sub);  // of the packed h
     const int row0 = __builtin_amdgcn_readfirstlane(s_off[it.slot] + it.sub * WT_M);
     const int nvalid = __builtin_amdgcn_readfirstlane(min(WT_M, s_cnt[it.slot] - it.sub * WT_M));
     // Epilogue.  Lane l of tile (i, j) holds token row 32 (2 i + wm) + l % 32
@@ -556,9 +563,9 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
       barrier_nofence();
       // chunk 4 (wn / 2) + 2 (wn & 1) + j of the row in step nbt of the down
       // GEMM: load 2 (wn / 2) + j, lane l % 32 + 32 (wn & 1)
-      char* hb = p.C + ((size_t)tile * (p.NB / 2) + nbt) * WT_STEP + (2 * (wn >> 1) + hl) * 1024 +
-                 (32 * (wn & 1) + l31) * 16;
-      float* hs = p.C_sc + ((size_t)tile * (p.NB / 2) + nbt) * WT_M;
+      const size_t at = piece * (p.NB / 2) + nbt * it.live;
+      char* hb = p.C + at * 4096 + (2 * (wn >> 1) + hl) * 1024 + (32 * (wn & 1) + l31) * 16;
+      float* hs = p.C_sc + at * 32;
 #pragma unroll
       for (int i = 0; i < NI; i++) {
         if (i >= nb) continue;
@@ -602,7 +609,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
       // columns 64 (wn / 2) + 16 p + 8 q + 4 hl + m of the item's 128 (p the
       // piece): chunk 2 p + q of step 2 nbt + wn / 2 of the down GEMM, i.e.
       // load p, lane l % 32 + 32 q
-      char* hb = p.C + ((size_t)tile * p.NB + 2 * nbt + (wn >> 1)) * WT_STEP + 2 * (wn & 1) * 1024 + lid * 16;
+      char* hb = p.C + (piece * p.NB + (2 * nbt + (wn >> 1)) * it.live) * 4096 + 2 * (wn & 1) * 1024 + lid * 16;
 #pragma unroll
       for (int i = 0; i < NI; i++) {
         if (i >= nb) continue;
@@ -663,7 +670,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     int ca_n = n0 - 1, ca_k = KT - 1, ca_h = 1, ca_u = WT_NA - 1;
     int cw_n = n0 - 1, cw_k = KT - 1, cw_s = 1;
     uint64_t a_base = 0, w_base = 0;
-    uint32_t a_blk[2] = {0, 0};
+    uint32_t a_blk[2] = {0, 0}, a_step = 0, sc_step = 0;
     const char* s_ptr = nullptr;
     // a half-step: this wavefront's 2 KB of it (row block 4 h + wave / 2, loads 2 (wave & 1) and + 1)
     uint64_t a_src = 0, w_src = 0;
@@ -675,13 +682,14 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
         ca_n = min(ca_n + 1, n1 - 1);
         const Item it = item(ca_n);
         a_base = a_of(it) + (wave & 1) * 2048;
+        a_step = it.live * 4096;
 #pragma unroll
         for (int h = 0; h < 2; h++) {
           const int b = 4 * h + (wave >> 1);
           a_blk[h] = __builtin_amdgcn_readfirstlane(b < it.live ? b * 4096 : 0);
         }
       }
-      a_src = a_base + (size_t)ca_k * WT_STEP + (ca_h ? a_blk[1] : a_blk[0]);
+      a_src = a_base + (size_t)ca_k * a_step + (ca_h ? a_blk[1] : a_blk[0]);
       a_dst = ring_lds + WT_A + ca_u * WT_UNIT + wave * 2048;
     };
     auto next_w = [&]() {
@@ -691,7 +699,10 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
         cw_n = min(cw_n + 1, n1 - 1);
         const Item it = item(cw_n);
         w_base = w_of(it);
-        if (F8) s_ptr = s_of(it);
+        if (F8) {
+          s_ptr = s_of(it);
+          sc_step = it.live * 128;
+        }
       }
       w_src = w_base + (size_t)cw_k * B_BYTES;
       w_dst = ring_lds + WT_W + cw_s * WT_STEP + wave * 4096;
@@ -700,7 +711,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     auto load_s = [&]() {
       if (F8) {
         lds_dma16v_lanes(s_ptr, s_dst, S_LANES);
-        s_ptr += s_inc;
+        s_ptr += lane < 8 ? sc_step : 16;
       }
     };
     auto load_a = [&]() {
@@ -809,6 +820,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     constexpr int L = 6 + SL;  // loads of a step
     int c_n = n0 - 1, c_k = KT - 1, c_s = NSL - 1;
     uint64_t a_base = 0, w_base = 0;
+    uint32_t a_step = 0;
     int a_b = 0;  // 1 where this wavefront's row block is live
     const char* s_ptr = nullptr;
     uint64_t a_src = 0, w_src = 0;
@@ -821,13 +833,14 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
         const Item it = item(c_n);
         w_base = w_of(it);
         a_base = a_of(it) + wave * 2048;
+        a_step = it.live * 4096;
         a_b = __builtin_amdgcn_readfirstlane((wave >> 1) < it.live ? 1 : 0);
         if (F8) s_ptr = s_of(it);
       }
       dst = ring_lds + c_s * SLOT;
       s_dst = ring_lds + WT_S + c_s * WT_SC + wave * WT_SCW;
       w_src = w_base + (size_t)c_k * B_BYTES;
-      a_src = a_base + (size_t)c_k * WT_STEP;
+      a_src = a_base + (size_t)c_k * a_step;
     };
     auto put_w = [&](int q) {
       if (q == 0) lds_dma16s_at<0>(w_src, lane16, dst + AB + wave * 4096);
@@ -839,7 +852,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     auto put_sa = [&](int q) {
       if (F8 && q == 0) {
         lds_dma16v_lanes(s_ptr, s_dst, S_LANES);
-        s_ptr += s_inc;
+        s_ptr += lane < 8 ? a_step / 32 : 16;
       }
       if (q == 1) lds_dma16s_x2_if(a_src, lane16, dst + wave * 2048, a_b);
       __builtin_amdgcn_sched_barrier(0);
@@ -984,7 +997,8 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 //          -> 408), 64: 164 -> 133, 128: 219 -> 164; short contractions
 //          (H 1152): 32: 68 -> 72, 96: 81 -> 74; items 73: 94 -> 91; against its
 //          own 256-row kernel 160: 173 -> 173, 512: 327 -> 333
-//   bf16   16: 178 -> 179, 32: 208 -> 202 (36 slots 854 -> 735), 64: 249 ->
+//   bf16   16: 178 -> 179, 32: 208 -> 202 (with a plan that leaves one slot
+//          of six live row blocks, 181 -> 191; 36 slots 854 -> 735), 64: 249 ->
 //          208 (36 slots with 128-row tiles 651 -> 669), 92: 305 -> 228, 187:
 //          316 -> 247, 512: 593 -> 551; items 133: 175 -> 191, 192 (10 slots):
 //          126 -> 138, 275 (10 slots): 160 -> 153
@@ -993,7 +1007,7 @@ bool experts_wide_wanted(const tempo_moe_shape& s) {
   const long long P = (long long)s.T * s.K, E = s.E;
   // items of the gate/up GEMM, were the pairs spread evenly over the experts
   const long long items = (s.S + P * s.S / (256 * E)) * (s.I / 128);
-  if (s.dtype == TEMPO_BF16) return items >= 200 && P >= (s.m_tile == 64 ? 32 : 80) * E;
+  if (s.dtype == TEMPO_BF16) return items >= 200 && P >= (s.m_tile == 64 ? 48 : 80) * E;
   if (s.dtype == TEMPO_FP8_E4M3) return items >= 80 && P >= 12 * E;
   return items >= 80 && P >= (s.H >= 2048 ? 24 : 64) * E;
 }

@@ -45,7 +45,7 @@ struct Layout {
   size_t fix;         // [grid][12] int32 stage-2 fixup records
   size_t total;
   // wide-tile kernels (wide_tiles > 0): packed activation tiles and their
-  // scales, packed h and its scales (within the regions above)
+  // scales, packed h and its scales (over regions above that are free then)
   size_t wide_a, wide_a_sc, wide_h, wide_h_sc;
   int wide_tiles;     // most 256-row tiles of a batch
   int nblk;
