@@ -38,12 +38,14 @@ hipError_t launch_bm(const tempo_moe_shape& s, const tempo_dispatch_out& d, cons
   gu.C = h;
   gu.Kd = s.H;
   gu.Nout = s.I;
-  gu.cmax = GATEUP_CHUNKS;
+  gu.cmax = gateup_chunks(s);
   auto mark = [&](int i) { return !ev || !ev[i] || hipEventRecord(ev[i], st) == hipSuccess; };
   if (!mark(0)) return hipErrorLaunchFailure;
   hipLaunchKernelGGL((k_gemm<false, BM, true>), dim3(grid), dim3(GEMM_THREADS), 0, st, gu);
   if (!mark(1)) return hipErrorLaunchFailure;
-  hipLaunchKernelGGL((k_fixup<false, BM, true>), dim3(grid * (BM / 8)), dim3(256), 0, st, gu, grid);
+  // (with one chunk per item no item is split: nothing to complete)
+  if (gu.cmax > 1)
+    hipLaunchKernelGGL((k_fixup<false, BM, true>), dim3(grid * (BM / 8)), dim3(256), 0, st, gu, grid);
   if (!mark(2)) return hipErrorLaunchFailure;
 
   // down -> y_perm [row_cap, H] bf16
@@ -60,7 +62,6 @@ hipError_t launch_bm(const tempo_moe_shape& s, const tempo_dispatch_out& d, cons
   dn.cmax = DOWN_CHUNKS;
   hipLaunchKernelGGL((k_gemm<false, BM, false>), dim3(grid), dim3(GEMM_THREADS), 0, st, dn);
   if (!mark(3)) return hipErrorLaunchFailure;
-  // (with one chunk per item no down item is split: nothing to complete)
   if (dn.cmax > 1)
     hipLaunchKernelGGL((k_fixup<false, BM, false>), dim3(grid * (BM / 8)), dim3(256), 0, st, dn, grid);
   return hipGetLastError();

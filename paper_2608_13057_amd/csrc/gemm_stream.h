@@ -9,7 +9,7 @@
 // Work decomposition (stream-K over fixed contraction chunks).  A work item
 // is one (M-tile, output block of 128 weight rows) pair; its contraction of
 // KT steps (128 bytes of every row per step) is cut into C fixed chunks of
-// SPC steps (C at most GemmArgs::cmax: 2 for gate/up, 1 for down), SPC a
+// SPC steps (C at most GemmArgs::cmax), SPC a
 // multiple of CQ = 8 for every tile size (the last chunk is padded with
 // empty steps to a multiple of the pipeline depth DR).  The chunks of all items,
 // item by item, form one sequence that is split into contiguous ranges, one
@@ -62,6 +62,7 @@
 // 16 bytes per lane.
 #pragma once
 
+#include <cmath>
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -109,12 +110,23 @@ struct GemmArgs {
 
 // Chunks per item of the two GEMMs (GemmArgs::cmax).  Fewer chunks mean
 // fewer items split over workgroups, so fewer partial tiles to write and add
-// up, against a coarser balance of the ranges.  Measured on the decode
-// shares (64- and 128-row tiles) and the fp8 prefill share: gate/up is
-// fastest with two chunks (its long contraction, H, leaves the ranges too
-// coarse at one), down with one (its output has many blocks, so whole items
-// balance well, and no fixup pass is needed).
-constexpr int GATEUP_CHUNKS = 2, DOWN_CHUNKS = 1;
+// up, and with one no fixup pass, against a coarser balance of the ranges.
+// Down takes one: its output has many blocks, so whole items balance well.
+// gate/up takes one where its contraction is short or its items are about as
+// many as the workgroups, and two for a few long items.  The slots that will
+// be active are only known on the device; the expected number, were the pairs
+// spread evenly over the experts, stands for them (the same for every plan and
+// M-tile).  Measured, forward us with two -> one (18 slots H 4096 I 1536
+// unless said): bf16 16 tokens 82 -> 74, 32: 94 -> 88, 256: 176 -> 169, 512:
+// 211 -> 207; fp8 16: 70 -> 62, 64: 86 -> 88; 36 slots H 7168 I 2048 fp8 64:
+// 228 -> 220; H 256: 33 -> 30; but bf16 4 tokens (96 expected items) 57 -> 58,
+// four slots of 96 items 57 -> 64, two slots H 7168 I 2048 (64 items) 60 -> 72.
+inline int gateup_chunks(const tempo_moe_shape& s) {
+  const int KT = s.H / (s.dtype == TEMPO_BF16 ? 64 : 128);
+  const double active = s.S * (1.0 - std::pow(1.0 - 1.0 / s.E, (double)s.T * s.K));
+  return KT <= 16 || active * (s.I / 64) >= 150.0 ? 1 : 2;
+}
+constexpr int DOWN_CHUNKS = 1;
 
 // Steps in flight per wavefront (DR): the weight slices of DR steps sit in
 // registers (four 16-byte loads per lane and step), the activation rows of
@@ -158,70 +170,83 @@ constexpr int W_BASE = 4;
 template <int BM>
 __device__ __forceinline__ int tile_weight(int rows) { return W_BASE + ((rows + 31) >> 5); }
 
-// All threads of the block; ends with a barrier.  s_off / s_cnt must be ready.
-// Wavefront 0 scans: lane l sums slots 4l..4l+3, then a shuffle scan.
+// By every wavefront for itself (all write the same s_sw); s_off / s_cnt must
+// be ready.  Lane l sums slots 4l .. 4l + 3, then a shuffle scan; end[i]:
+// s_sw of slot 4l + i + 1 (the sum up to and with slot 4l + i).
 template <int BM>
-__device__ void build_slot_weights(const int32_t* s_off, const int32_t* s_cnt, int32_t* s_sw, int S) {
+__device__ __forceinline__ void build_slot_weights(const int32_t* s_off, const int32_t* s_cnt, int32_t* s_sw, int S,
+                                                   int (&end)[4]) {
   static_assert(kMaxS <= 256, "four slots per lane");
-  if (threadIdx.x < 64) {
-    const int l = threadIdx.x;
-    int w[4], run = 0;
+  const int l = threadIdx.x & 63;
+  int run = 0;
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int s = 4 * l + i;
-      int v = 0;
-      if (s < S) {
-        const int nt = (s_off[s + 1] - s_off[s]) / BM;
-        v = nt > 0 ? (nt - 1) * tile_weight<BM>(BM) + tile_weight<BM>(s_cnt[s] - (nt - 1) * BM) : 0;
-      }
-      run += v;
-      w[i] = run;
+  for (int i = 0; i < 4; i++) {
+    const int s = 4 * l + i;
+    int v = 0;
+    if (s < S) {
+      const int nt = (s_off[s + 1] - s_off[s]) / BM;
+      v = nt > 0 ? (nt - 1) * tile_weight<BM>(BM) + tile_weight<BM>(s_cnt[s] - (nt - 1) * BM) : 0;
     }
-    int incl = run;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = __shfl_up(incl, d);
-      if (l >= d) incl += o;
-    }
-    const int excl = incl - run;
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-      if (4 * l + i < S) s_sw[4 * l + i + 1] = excl + w[i];
-    if (l == 0) s_sw[0] = 0;
+    run += v;
+    end[i] = run;
   }
-  __syncthreads();
+  int incl = run;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(incl, d);
+    if (l >= d) incl += o;
+  }
+  const int excl = incl - run;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    end[i] += excl;
+    if (4 * l + i < S) s_sw[4 * l + i + 1] = end[i];
+  }
+  if (l == 0) s_sw[0] = 0;
+  wait_lgkm0();
 }
 
 // First chunk of workgroup j of a group: the smallest chunk q whose weight
-// prefix reaches j / wpx of the total.
-template <int BM>
-__device__ int range_lo(const Geo& g, int j, const int32_t* s_off, const int32_t* s_cnt, const int32_t* s_sw, int S) {
+// prefix reaches j / wpx of the total.  INT: the type of the arithmetic (32
+// bits where unit * s_sw[S] * wpx fits).  first(unit, T): the first slot whose
+// end, unit * s_sw[s + 1], lies beyond T.
+template <int BM, typename INT, typename F>
+__device__ __forceinline__ int range_from(const Geo& g, int j, const int32_t* s_off, const int32_t* s_cnt,
+                                          const int32_t* s_sw, int S, F first) {
   const int U = g.items * g.C;
   if (j <= 0) return 0;
   if (j >= g.wpx) return U;
-  const long long unit = (long long)g.my_nb * g.C;  // chunks per M-tile
-  const long long T = unit * s_sw[S] * j / g.wpx;   // target weight
-  // the first slot whose end lies beyond T
-  int lo = 0, hi = S;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (unit * s_sw[mid + 1] > T) hi = mid;
-    else lo = mid + 1;
-  }
+  const INT unit = (INT)g.my_nb * g.C;       // chunks per M-tile
+  const INT T = unit * s_sw[S] * j / g.wpx;  // target weight
+  const int lo = first(unit, T);
   if (lo == S) return U;
   const int nt = (s_off[lo + 1] - s_off[lo]) / BM;  // >= 1
-  const long long wf = unit * tile_weight<BM>(BM);
-  const long long rem = T - unit * s_sw[lo];
-  const long long tf = min(rem / wf, (long long)(nt - 1));  // whole tiles of the slot before the target
+  const INT wf = unit * tile_weight<BM>(BM);
+  const INT rem = T - unit * s_sw[lo];
+  const INT tf = min(rem / wf, (INT)(nt - 1));  // whole tiles of the slot before the target
   const int wt = tf < nt - 1 ? tile_weight<BM>(BM) : tile_weight<BM>(s_cnt[lo] - (nt - 1) * BM);
-  const long long r = min((rem - tf * wf + wt - 1) / wt, unit);
+  const INT r = min((INT)((rem - tf * wf + wt - 1) / wt), unit);
   const long long q = (long long)(s_off[lo] / BM + tf) * unit + r;
   return (int)min(q, (long long)U);
 }
 
 template <int BM>
+__device__ int range_lo(const Geo& g, int j, const int32_t* s_off, const int32_t* s_cnt, const int32_t* s_sw, int S) {
+  return range_from<BM, long long>(g, j, s_off, s_cnt, s_sw, S, [&](long long unit, long long T) {
+    int lo = 0, hi = S;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (unit * s_sw[mid + 1] > T) hi = mid;
+      else lo = mid + 1;
+    }
+    return lo;
+  });
+}
+
+template <int BM>
 __device__ __forceinline__ Geo make_geo(int KT, int NB, int NT, int b, int grid, const int32_t* s_off,
-                                        const int32_t* s_cnt, const int32_t* s_sw, int S, int cmax) {
+                                        const int32_t* s_cnt, const int32_t* s_sw, int S, int cmax,
+                                        const int (&end)[4]) {
   Geo g;
   constexpr int DR = gemm_dr(BM);
   g.KT = KT;
@@ -237,8 +262,25 @@ __device__ __forceinline__ Geo make_geo(int KT, int NB, int NT, int b, int grid,
   g.my_nb = NB / g.groups;
   g.nb_lo = g.grp * g.my_nb;
   g.items = NT * g.my_nb;
-  g.q0 = range_lo<BM>(g, g.j0, s_off, s_cnt, s_sw, S);
-  g.q1 = range_lo<BM>(g, g.j0 + 1, s_off, s_cnt, s_sw, S);
+  // (by the whole wavefront: the first slot beyond T by ballots on the slot
+  // weights in registers, and 32-bit divisions wherever they do; with a 64-bit
+  // binary search this took most of 4 us before the first load)
+  const int l = threadIdx.x & 63;
+  auto first = [&](auto unit, auto T) {
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) n += __popcll(__ballot(4 * l + i < S && unit * end[i] <= T));
+    return n;
+  };
+  if ((long long)g.my_nb * g.C * s_sw[S] * g.wpx < (1ll << 31)) {
+    g.q0 = range_from<BM, int>(g, g.j0, s_off, s_cnt, s_sw, S, first);
+    g.q1 = range_from<BM, int>(g, g.j0 + 1, s_off, s_cnt, s_sw, S, first);
+  } else {
+    g.q0 = range_from<BM, long long>(g, g.j0, s_off, s_cnt, s_sw, S, first);
+    g.q1 = range_from<BM, long long>(g, g.j0 + 1, s_off, s_cnt, s_sw, S, first);
+  }
+  g.q0 = __builtin_amdgcn_readfirstlane(g.q0);
+  g.q1 = __builtin_amdgcn_readfirstlane(g.q1);
   return g;
 }
 
@@ -299,15 +341,24 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void k_gemm(const GemmArgs p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  for (int s = tid; s <= p.S; s += GEMM_THREADS) s_off[s] = p.slot_offsets[s];
-  for (int s = tid; s < p.S; s += GEMM_THREADS) s_cnt[s] = p.slot_counts[s];
+  {
+    // (both arrays' loads in flight together: S <= 256 = the threads)
+    static_assert(kMaxS <= GEMM_THREADS, "one slot per thread");
+    const int o = tid <= p.S ? p.slot_offsets[tid] : 0, c = tid < p.S ? p.slot_counts[tid] : 0;
+    const int last = p.S == GEMM_THREADS && tid == 0 ? p.slot_offsets[GEMM_THREADS] : 0;
+    if (tid <= p.S) s_off[tid] = o;
+    if (tid < p.S) s_cnt[tid] = c;
+    if (p.S == GEMM_THREADS && tid == 0) s_off[GEMM_THREADS] = last;
+  }
   __syncthreads();
-  build_slot_weights<BM>(s_off, s_cnt, s_sw, p.S);
+  int sw_end[4];
+  build_slot_weights<BM>(s_off, s_cnt, s_sw, p.S, sw_end);
 
   // M-tiles in use, from the stage-1 offsets themselves (every P_s is a
   // multiple of BM), bounded by what the row buffers hold
   const int NT = __builtin_amdgcn_readfirstlane(max(0, min(s_off[p.S] / BM, p.max_tiles)));
-  const Geo g = make_geo<BM>(p.Kd / BK, p.Nout / NCOLS, NT, blockIdx.x, gridDim.x, s_off, s_cnt, s_sw, p.S, p.cmax);
+  const Geo g = make_geo<BM>(p.Kd / BK, p.Nout / NCOLS, NT, blockIdx.x, gridDim.x, s_off, s_cnt, s_sw, p.S, p.cmax,
+                             sw_end);
   if (g.q0 >= g.q1) {  // uniform: the whole workgroup leaves
     if (tid == 0) p.fix[(size_t)blockIdx.x * FIX_WORDS] = -1;
     return;
@@ -326,9 +377,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void k_gemm(const GemmArgs p) {
     const int nt = min(last_item / g.my_nb - tile_lo + 1, NROWT);
     for (int t = wave; t < nt; t += 4)
       if (lane < BM / 4) lds_dma16(p.row_src + (size_t)(tile_lo + t) * BM + lane * 4, &s_rows[t][0]);
-    __builtin_amdgcn_s_waitcnt(TEMPO_VMCNT_IMM(0));
   }
-  barrier_nofence();
 
   // A ring slot holds the activation row groups of the range's largest M-tile
   // (and the step's scales for fp8).
@@ -341,6 +390,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void k_gemm(const GemmArgs p) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) amax = max(amax, __shfl_xor(amax, d));
   const int A_BYTES = __builtin_amdgcn_readfirstlane(((amax + 7) >> 3) * 1024);
+  if (gather) __builtin_amdgcn_s_waitcnt(TEMPO_VMCNT_IMM(0));  // the row tables (meanwhile, amax)
+  barrier_nofence();
   const int SLOT = A_BYTES + EXTRA;
 
   // steps of the range: SPC per chunk, SL for an item's last chunk
