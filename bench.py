@@ -319,7 +319,8 @@ def roofline(m, copy_gbs=None):
 
     wl = m.wl
     gu_s = m.kernel_us["gate_up_gemm"] * 1e-6
-    kernel = measure.gateup_kernel_name(wl.dtype, m.m_tile, wl.H, wl.I)
+    wide = measure.uses_wide_kernel(wl, m.m_tile)
+    kernel = measure.gateup_kernel_name(wl.dtype, m.m_tile, wl.H, wl.I, wide)
     traffic, traffic_current = measure.committed_traffic(m.name, m.m_tile)
     common = {"traffic": traffic if traffic_current else None, "kernel": kernel + " (gate/up)",
               "launch_us": m.kernel_us["gate_up_gemm"], "G": m.G, "N": m.N}

@@ -40,6 +40,13 @@
 //   row blocks, groups of 4 tiles x all weight blocks, runs per XCD, rounds
 //   alternately forwards and backwards; every second XCD works through its
 //   items from the small end.  Row blocks of padding only are not computed.
+//   What whole rounds leave over goes by halves of items (one weight block of
+//   128 rows; four wavefront rows x two, three to seven slots of whole steps),
+//   but for fp8 gate/up, whose h scale spans both blocks: the last round is
+//   the small tiles', and a chip half filled with whole items waits for their
+//   latency.  Measured: 4097 tokens of 10 slots H 2048 I 1408, UE8M0 down 31.7
+//   -> 23.4 us; bf16 18 slots, 1499 tokens, gate/up 129 -> 123, 4096 rows of 512
+//   tokens down 61 -> 55, 11486 rows gate/up 295 -> 286.
 //   Items are never split: a row's sums run over its steps in order, so its
 //   result depends on its own inputs alone.
 // * gate/up epilogue: SwiGLU; fp8: the amax of each row over the item's 128
@@ -64,7 +71,7 @@ constexpr int WT_SC = 8 * WT_SCW;            // scales of a step (fp8)
 constexpr int WT_A = 0;                      // LDS ring: activations,
 constexpr int WT_W = WT_NA * WT_UNIT;        //   weights (2 slots),
 constexpr int WT_S = WT_W + 2 * WT_STEP;     //   scales (up to 4 slots)
-constexpr int WT_RING = WT_S + 4 * WT_SC;
+                                             //   (4 slots, or 7 where items are halved)
 constexpr int WT_MAX_SORT = 768;             // tiles the cost-ordered list covers (beyond: tile order)
 constexpr int WT_GM = 4;                     // tiles per group of the item order
 
@@ -283,7 +290,10 @@ template <int DT, bool GATEUP>
 __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
   constexpr bool F8 = DT != kWideBf16, MX = DT == kWideMX;
   constexpr int SL = F8 ? 1 : 0;             // scale loads per wavefront and step
-  __shared__ __attribute__((aligned(1024))) char ring[WT_RING];
+  // the last, partly filled rounds go by halves of items (one weight block),
+  // but for fp8 gate/up, which quantises h over both blocks' columns
+  constexpr bool HALVES = !(F8 && GATEUP);
+  __shared__ __attribute__((aligned(1024))) char ring[WT_S + (HALVES ? 7 : 4) * WT_SC];
   __shared__ float xamax[4][WT_M];
   __shared__ int32_t s_off[kMaxS], s_cnt[kMaxS], s_st[kMaxS + 1];
   __shared__ uint32_t s_ord[WT_MAX_SORT];    // slot | (wide tile within the slot) << 8, in cost order
@@ -341,16 +351,28 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
   const int items = NT * NBT;
   const int G = gridDim.x;
   const int lin0 = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
+  // `full` whole rounds of items, then what is left in halves
   const int full = items / G;
-  const int my_items = full + (((full & 1) ? G - 1 - lin0 : lin0) < items - full * G ? 1 : 0);
+  int rest = items - full * G, rounds = full;
+  if (HALVES) {
+    rest *= 2;
+    if (rest >= G) rest -= G, rounds++;
+  }
+  const int my_items = rounds + (((rounds & 1) ? G - 1 - lin0 : lin0) < rest ? 1 : 0);
   if (my_items == 0) return;
-  // item n of this workgroup: slot | sub << 8, and the pair of weight blocks.
-  // Every second XCD takes its items the other way round, the small ones
-  // first: tiles of few rows wait for their weights, full ones for the matrix
-  // pipes, and the two kinds run side by side.
-  auto item_of = [&](int n, int& nbt) {
+  // Item n of this workgroup: slot | sub << 8, the pair of weight blocks, and
+  // which of the two (-1: both).  Every second XCD takes its items the other
+  // way round, the small ones first: tiles of few rows wait for their weights,
+  // full ones for the matrix pipes, and the two kinds run side by side.
+  auto item_of = [&](int n, int& nbt, int& half) {
     if (blockIdx.x & 1) n = my_items - 1 - n;
-    const int it = n * G + ((n & 1) ? G - 1 - lin0 : lin0);
+    int it = n * G + ((n & 1) ? G - 1 - lin0 : lin0);
+    half = -1;
+    if (HALVES && n >= full) {
+      const int j = it - full * G;
+      it = full * G + (j >> 1);
+      half = j & 1;
+    }
     const int grp = it / (WT_GM * NBT), w_in = it - grp * (WT_GM * NBT);
     const int gm = min(WT_GM, NT - grp * WT_GM);
     nbt = w_in / gm;
@@ -369,27 +391,28 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
   const uint32_t ring_lds = lds_addr(ring);
   const uint32_t lane16 = lane * 16;
   struct Item {
-    int slot, sub, nbt, live;
+    int slot, sub, nbt, half, live;
   };
   auto item = [&](int n) {
     Item it;
-    const uint32_t d = item_of(n, it.nbt);
+    const uint32_t d = item_of(n, it.nbt, it.half);
     it.slot = d & 255;
     it.sub = d >> 8;
     it.live = __builtin_amdgcn_readfirstlane(live_of(d));
     return it;
   };
-  // this wavefront's weight piece of an item: piece wave of the eight (the
-  // second block of the last item of an odd number of blocks is the first again)
+  // this wavefront's weights of an item: piece wave of the eight, or half a
+  // piece of a half's four (a block past the last one is the last one again,
+  // read by nobody)
   auto table = [&]() {
     const uint64_t* t = p.wtab;  // (through an empty asm: see item_of)
     asm volatile("" : "+s"(t));
     return t;
   };
   auto w_of = [&](const Item& it) {
-    const int blk = min(2 * it.nbt + (wave >> 2), p.NB - 1);
+    const int blk = min(2 * it.nbt + (it.half < 0 ? wave >> 2 : it.half), p.NB - 1);
     return uni((uint64_t)(uintptr_t)slot_tensor(p.W, p.w_slot_bytes, table(), p.wfield, it.slot) +
-               (size_t)blk * KT * B_BYTES + (wave & 3) * 4096);
+               (size_t)blk * KT * B_BYTES + (it.half < 0 ? (wave & 3) * 4096 : wave * 2048));
   };
   auto a_of = [&](const Item& it) {
     return uni((uint64_t)(uintptr_t)p.A + wide_piece(s_off[it.slot], it.sub) * KT * 4096);
@@ -397,12 +420,20 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
   // fp8 scales of a step, one load: lanes 0 .. 7 those of rows 32 wave .. 32
   // wave + 31 (of the last live block for the dead ones), lanes 8 and 9 those
   // of the two weight blocks
+  auto fresh_lane = []() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+  };
   auto s_of = [&](const Item& it) {
     const char* ws =
         slot_tensor(reinterpret_cast<const char*>(p.Wsp), p.ws_slot_floats * 4, table(), p.sfield, it.slot);
     const char* as =
         reinterpret_cast<const char*>(p.A_sc + (wide_piece(s_off[it.slot], it.sub) * KT + min(wave, it.live - 1)) * 32);
-    return lane < 8 ? as + lane16 : ws + (size_t)min(2 * it.nbt + (lane == 9 ? 1 : 0), p.NB - 1) * KT * 16;
+    // (the lane and what is made of it anew: spilled, its reload would wait for the DMAs)
+    const int l = fresh_lane();
+    const int blk = min(2 * it.nbt + (it.half < 0 ? (l == 9 ? 1 : 0) : it.half), p.NB - 1);
+    return l < 8 ? as + l * 16 : ws + (size_t)blk * KT * 16;
   };
   constexpr uint64_t S_LANES = 0x3FFull;
 
@@ -415,24 +446,24 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     const i32x4 hi = *reinterpret_cast<const i32x4*>(s + 1024);
     return (i32x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   };
-  // (the parts of this wavefront: w the weights of a step, a the rows of a half-step)
+  // two pieces of weights from w, a row block from a into buffer i, the scales
+  // of ring slot `slot` for row blocks rb0 + rbs i and weight block `blk` of the item
   auto read_b = [&](const char* w, int j) {
-    const char* s = w + wn * 8192 + lane16 + j * 4096;
 #pragma unroll
-    for (int h = 0; h < 2; h++) fb[j][h] = rd8(s + h * 2048);
-  };
-  auto read_s = [&](int slot) {
-    const char* s = ring + WT_S + slot * WT_SC + wm * WT_SCW + (lane & 31) * 4;
-#pragma unroll
-    for (int i = 0; i < 4; i++) sa[i] = *reinterpret_cast<const float*>(s + 2 * i * WT_SCW);
-    const float2 v = *reinterpret_cast<const float2*>(ring + WT_S + slot * WT_SC + 128 + 16 * (wn >> 1));
-    sw0 = v.x;
-    sw1 = GATEUP ? v.y : v.x;
+    for (int h = 0; h < 2; h++) fb[j][h] = rd8(w + lane16 + j * 4096 + h * 2048);
   };
   auto read_a = [&](const char* a, int i) {
-    const char* s = a + wm * 4096 + lane16 + 8192 * (i & 1);
 #pragma unroll
-    for (int h = 0; h < 2; h++) fa[i & 1][h] = rd8(s + h * 2048);
+    for (int h = 0; h < 2; h++) fa[i & 1][h] = rd8(a + lane16 + h * 2048);
+  };
+  auto read_s = [&](auto ni, int slot, int rb0, int rbs, int blk) {
+    const char* s = ring + WT_S + slot * WT_SC;
+#pragma unroll
+    for (int i = 0; i < decltype(ni)::value; i++)
+      sa[i] = *reinterpret_cast<const float*>(s + (rb0 + rbs * i) * WT_SCW + (lane & 31) * 4);
+    const float2 v = *reinterpret_cast<const float2*>(s + 128 + 16 * blk);
+    sw0 = v.x;
+    if (GATEUP) sw1 = v.y;
   };
   auto ue = [](float s) { return (int)((__float_as_uint(s) >> 23) & 0xFF); };
   // acc of row block i += its rows times this wavefront's weight rows, over
@@ -483,7 +514,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
       }
       __builtin_amdgcn_sched_barrier(0);
       // elements 0 .. 7 belong to the gate rows of a piece, 8 .. 15 to the up rows
-      const float s0 = sa[i] * sw0, s1 = sa[i] * sw1;
+      const float s0 = sa[i] * sw0, s1 = GATEUP ? sa[i] * sw1 : s0;
 #pragma unroll
       for (int j = 0; j < 2; j++)
 #pragma unroll
@@ -493,9 +524,10 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
   };
   auto nothing = [](int) {};
 
-  // Start and end of an item: NI row blocks of this wavefront at most.
+  // Start and end of an item: this wavefront's row blocks rb0 + rbs i (i < NI;
+  // live ones: i < nb) against the weight rows 64 g .. of the item's 256.
   struct Out {
-    int n, nb;
+    int n, nb, rb0, rbs, g;
     uint64_t tstart;
   };
   auto begin = [&](auto ni, int n) {
@@ -503,10 +535,14 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     const Item it = item(n);
     Out o;
     o.n = n;
-    // live row blocks 2 i + wm, i < nb, of this wavefront (none where its
-    // weight block is past the last one)
-    o.nb = 2 * it.nbt + (wn >> 1) < p.NB ? (it.live + 1 - wm) >> 1 : 0;
-    o.tstart = p.timing ? __builtin_amdgcn_s_memrealtime() : 0;
+    o.rb0 = it.half < 0 ? wm : wave >> 1;
+    o.rbs = it.half < 0 ? 2 : 4;
+    o.g = it.half < 0 ? wn : 2 * it.half + (wave & 1);
+    // (none live where its weight block is past the last one)
+    o.nb = 2 * it.nbt + (o.g >> 1) < p.NB ? (it.half < 0 ? (it.live + 1 - o.rb0) >> 1 : (it.live + 3 - o.rb0) >> 2) : 0;
+    int timing = p.timing;
+    asm volatile("" : "+s"(timing));
+    o.tstart = timing ? __builtin_amdgcn_s_memrealtime() : 0;
 #pragma unroll
     for (int i = 0; i < NI; i++)
 #pragma unroll
@@ -518,16 +554,15 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
   auto finish = [&](auto ni, const Out& o) {
     constexpr int NI = decltype(ni)::value;
     const Item it = item(o.n);
-    const int nbt = it.nbt, nb = o.nb;
+    const int nbt = it.nbt, nb = o.nb, g = o.g;
     const size_t piece = wide_piece(s_off[it.slot], it.sub);  // of the packed h
     const int row0 = __builtin_amdgcn_readfirstlane(s_off[it.slot] + it.sub * WT_M);
     const int nvalid = __builtin_amdgcn_readfirstlane(min(WT_M, s_cnt[it.slot] - it.sub * WT_M));
-    // Epilogue.  Lane l of tile (i, j) holds token row 32 (2 i + wm) + l % 32
+    // Epilogue.  Lane l of tile (i, j) holds token row 32 (rb0 + rbs i) + l % 32
     // and, in element e, packed weight row 8 (e / 4) + 4 (l / 32) + e % 4 of
-    // piece 2 (wn & 1) + j of block 2 nbt + wn / 2 (gate/up: rows 0 .. 15
+    // piece 2 (g & 1) + j of block 2 nbt + g / 2 (gate/up: rows 0 .. 15
     // gate, 16 .. 31 up, so a column's gate and up are elements e and e + 8).
-    int lid;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lid));
+    const int lid = fresh_lane();
     const int l31 = lid & 31, hl = lid >> 5;
     auto pack4 = [](float v0, float v1, float v2, float v3) {
       uint2 w;
@@ -557,19 +592,19 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
             m = fmaxf(m, fabsf(h));
           }
         m = fmaxf(m, __shfl_xor(m, 32));
-        if (hl == 0) xamax[wn][32 * (2 * i + wm) + l31] = m;
+        if (hl == 0) xamax[g][32 * (o.rb0 + o.rbs * i) + l31] = m;
       }
       wait_lgkm0();
       barrier_nofence();
-      // chunk 4 (wn / 2) + 2 (wn & 1) + j of the row in step nbt of the down
-      // GEMM: load 2 (wn / 2) + j, lane l % 32 + 32 (wn & 1)
+      // chunk 4 (g / 2) + 2 (g & 1) + j of the row in step nbt of the down
+      // GEMM: load 2 (g / 2) + j, lane l % 32 + 32 (g & 1)
       const size_t at = piece * (p.NB / 2) + nbt * it.live;
-      char* hb = p.C + at * 4096 + (2 * (wn >> 1) + hl) * 1024 + (32 * (wn & 1) + l31) * 16;
+      char* hb = p.C + at * 4096 + (2 * (g >> 1) + hl) * 1024 + (32 * (g & 1) + l31) * 16;
       float* hs = p.C_sc + at * 32;
 #pragma unroll
       for (int i = 0; i < NI; i++) {
         if (i >= nb) continue;
-        const int r = 32 * (2 * i + wm) + l31;
+        const int r = 32 * (o.rb0 + o.rbs * i) + l31;
         const float mm = fmaxf(fmaxf(xamax[0][r], xamax[1][r]), fmaxf(xamax[2][r], xamax[3][r]));
         float sc = mm > 0.f ? mm / 448.0f : 1.0f;
         if (MX && mm > 0.f) {
@@ -577,7 +612,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
           if (bits & 0x7FFFFFu) bits = (bits & 0xFF800000u) + 0x800000u;  // next power of two up
           sc = __uint_as_float(bits);
         }
-        if (wn == 0 && hl == 0) hs[r] = sc;
+        if (g == 0 && hl == 0) hs[r] = sc;
         // h / sc, correctly rounded from the reciprocal (Markstein 1990: r =
         // 1 / sc, q0 = h r, q = q0 + (h - q0 sc) r); tiny rows are scaled up
         // so that r stays finite, and an infinite sc gives 0 or NaN like the
@@ -603,13 +638,13 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
         // dword gives lane l the chunk of j = 0, lane l + 32 that of j = 1
         const auto x = __builtin_amdgcn_permlane32_swap(w[0][0], w[0][1], false, false);
         const auto y = __builtin_amdgcn_permlane32_swap(w[1][0], w[1][1], false, false);
-        *reinterpret_cast<i32x4*>(hb + (2 * i + wm) * 4096) = i32x4{(int)x[0], (int)x[1], (int)y[0], (int)y[1]};
+        *reinterpret_cast<i32x4*>(hb + (o.rb0 + o.rbs * i) * 4096) = i32x4{(int)x[0], (int)x[1], (int)y[0], (int)y[1]};
       }
     } else if constexpr (GATEUP) {
-      // columns 64 (wn / 2) + 16 p + 8 q + 4 hl + m of the item's 128 (p the
-      // piece): chunk 2 p + q of step 2 nbt + wn / 2 of the down GEMM, i.e.
+      // columns 64 (g / 2) + 16 p + 8 q + 4 hl + m of the item's 128 (p the
+      // piece): chunk 2 p + q of step 2 nbt + g / 2 of the down GEMM, i.e.
       // load p, lane l % 32 + 32 q
-      char* hb = p.C + (piece * p.NB + (2 * nbt + (wn >> 1)) * it.live) * 4096 + 2 * (wn & 1) * 1024 + lid * 16;
+      char* hb = p.C + (piece * p.NB + (2 * nbt + (g >> 1)) * it.live) * 4096 + 2 * (g & 1) * 1024 + lid * 16;
 #pragma unroll
       for (int i = 0; i < NI; i++) {
         if (i >= nb) continue;
@@ -621,16 +656,16 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
           for (int q = 0; q < 2; q++)
             w[q] = pack4(silu_mul(v[4 * q], v[4 * q + 8]), silu_mul(v[4 * q + 1], v[4 * q + 9]),
                          silu_mul(v[4 * q + 2], v[4 * q + 10]), silu_mul(v[4 * q + 3], v[4 * q + 11]));
-          *reinterpret_cast<i32x4*>(hb + (2 * i + wm) * 4096 + j * 1024) = swap16(w[0], w[1]);
+          *reinterpret_cast<i32x4*>(hb + (o.rb0 + o.rbs * i) * 4096 + j * 1024) = swap16(w[0], w[1]);
         }
       }
     } else {
-      char* yb = p.C + (size_t)row0 * p.ld_out + (size_t)(256 * nbt + 64 * wn + 8 * hl) * 2;
+      char* yb = p.C + (size_t)row0 * p.ld_out + (size_t)(256 * nbt + 64 * g) * 2;
 #pragma unroll
       for (int i = 0; i < NI; i++) {
         if (i >= nb) continue;
-        const int r = 32 * (2 * i + wm) + l31;
-        char* yr = yb + (size_t)r * p.ld_out;
+        const int r = 32 * (o.rb0 + o.rbs * i) + l31;
+        const uint32_t yr = (uint32_t)r * (uint32_t)p.ld_out + 16 * hl;
 #pragma unroll
         for (int j = 0; j < 2; j++) {
           const f32x16& v = acc[i][j];
@@ -639,13 +674,15 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
           for (int q = 0; q < 4; q++) w[q] = pack4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
           const i32x4 c0 = swap16(w[0], w[1]), c1 = swap16(w[2], w[3]);
           if (r < nvalid) {  // padding rows of y_perm stay unwritten
-            *reinterpret_cast<i32x4*>(yr + (32 * j) * 2) = c0;
-            *reinterpret_cast<i32x4*>(yr + (32 * j + 16) * 2) = c1;
+            *reinterpret_cast<i32x4*>(yb + yr + (32 * j) * 2) = c0;
+            *reinterpret_cast<i32x4*>(yb + yr + (32 * j + 16) * 2) = c1;
           }
         }
       }
     }
-    if (p.timing && tid == 0) {
+    int timing = p.timing;
+    asm volatile("" : "+s"(timing));
+    if (timing && wave == 0 && lid == 0) {
       const uint64_t tend = __builtin_amdgcn_s_memrealtime();
       atomicMin(reinterpret_cast<unsigned long long*>(&p.t0[it.slot]), (unsigned long long)o.tstart);
       atomicMax(reinterpret_cast<unsigned long long*>(&p.t1[it.slot]), (unsigned long long)tend);
@@ -754,8 +791,10 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     constexpr std::integral_constant<int, 8 + SL> in_flight{};
     auto unit_at = [](int u) { return u >= WT_NA ? u - WT_NA : u; };
     int u_rd = 0, w_rd = 0;  // ring positions of the step: its first half-step, its weights
-    auto a_at = [&](int u) { return ring + WT_A + u * WT_UNIT; };
-    auto w_at = [&](int s) { return ring + WT_W + s * WT_STEP; };
+    // (this wavefront's row block i of the half-step in place u, its weights in slot s)
+    auto a_at = [&](int u, int i) { return ring + WT_A + u * WT_UNIT + wm * 4096 + 8192 * (i & 1); };
+    auto w_at = [&](int s) { return ring + WT_W + s * WT_STEP + wn * 8192; };
+    auto scales = [&](int s) { read_s(std::integral_constant<int, 4>{}, s, wm, 2, wn >> 1); };
     load_w();
     load_a();
     load_a();
@@ -763,9 +802,9 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     load_a();
     load_a();
     sync(std::integral_constant<int, 10 + SL>{});
-    read_a(a_at(0), 0);
+    read_a(a_at(0, 0), 0);
     read_b(w_at(0), 0);
-    if (MX) read_s(0);
+    if (MX) scales(0);
 #pragma unroll 1
     for (int n = n0; n < n1; n++) {
       const Out o = begin(std::integral_constant<int, 4>{}, n);
@@ -773,8 +812,8 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
 #pragma unroll 1
       for (int k = 0; k < KT; k++) {
         read_b(w_at(w_rd), 1);
-        read_a(a_at(u_rd), 1);
-        if (F8 && !MX) read_s(w_rd);
+        read_a(a_at(u_rd, 1), 1);
+        if (F8 && !MX) scales(w_rd);
         __builtin_amdgcn_sched_barrier(0);
         if (0 < nb) mul(0, nothing);
         sync(in_flight);
@@ -782,18 +821,18 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
         next_a();
         w_rd ^= 1;
         u_rd = unit_at(u_rd + 1);
-        read_a(a_at(u_rd), 2);
+        read_a(a_at(u_rd, 2), 2);
         __builtin_amdgcn_sched_barrier(0);
         if (1 < nb) mul(1, put_w);
         else all(put_w);
-        read_a(a_at(u_rd), 3);
+        read_a(a_at(u_rd, 3), 3);
         __builtin_amdgcn_sched_barrier(0);
         if (2 < nb) mul(2, put_sa);
         else all(put_sa);
         sync(in_flight);
         next_a();
         u_rd = unit_at(u_rd + 1);
-        read_a(a_at(u_rd), 0);
+        read_a(a_at(u_rd, 0), 0);
         __builtin_amdgcn_sched_barrier(0);
         auto put_ab = [&](int q) {
           if (q == 0) lds_dma16s_at<0>(a_src, lane16, a_dst);
@@ -803,28 +842,33 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
         };
         if (3 < nb) mul(3, put_ab);
         else all(put_ab);
-        if (MX) read_s(w_rd);
+        if (MX) scales(w_rd);
       }
       finish(std::integral_constant<int, 4>{}, o);
     }
   };
 
-  // ---- items n0 .. n1 - 1, tiles of at most four live row blocks ----
-  // These wait for their weights, so the ring holds whole steps instead, of
-  // the weights and up to ab row blocks: three of 48 KB, or four of 36 KB for
-  // tiles of one live row block.
-  auto run_narrow = [&](int n0, int n1, auto nslc) {
-    constexpr int NSL = decltype(nslc)::value;
-    constexpr int AB = NSL == 4 ? 4096 : WT_UNIT, SLOT = WT_STEP + AB;
+  // ---- items n0 .. n1 - 1, tiles of at most four live row blocks, and halves ----
+  // These wait for their weights, so the ring holds whole steps instead: AB
+  // bytes of activations (all live row blocks), then 32 KB of weights (16 KB
+  // for halves), as many slots as fit.  Whole items as above; halves: row
+  // blocks wave / 2 + 4 i against 64 of the 128 weight rows.
+  auto run_small = [&](int n0, int n1, auto halfc, auto nslc, auto abc) {
+    constexpr bool HALF = decltype(halfc)::value;
+    constexpr int NSL = decltype(nslc)::value, AB = decltype(abc)::value;
+    constexpr int SLOT = AB + (HALF ? WT_UNIT : WT_STEP);
     static_assert(NSL * SLOT <= WT_S, "the ring holds the slots");
-    constexpr int L = 6 + SL;  // loads of a step
+    constexpr bool ALL_A = AB == WT_STEP;              // eight row blocks: one per wavefront (else half of one)
+    constexpr int NI = HALF && !ALL_A ? 1 : 2;         // row blocks of a wavefront
+    constexpr int L = (HALF ? 2 : 4) + SL + (ALL_A ? 4 : 2);  // loads of a step
+    constexpr std::integral_constant<int, NI> ni{};
     int c_n = n0 - 1, c_k = KT - 1, c_s = NSL - 1;
     uint64_t a_base = 0, w_base = 0;
     uint32_t a_step = 0;
-    int a_b = 0;  // 1 where this wavefront's row block is live
+    int a_b = 0;  // 1 where the row block this wavefront loads is live
     const char* s_ptr = nullptr;
     uint64_t a_src = 0, w_src = 0;
-    uint32_t dst = 0, s_dst = 0;
+    uint32_t a_dst = 0, w_dst = 0, s_dst = 0;
     auto next = [&]() {
       if (++c_s == NSL) c_s = 0;
       if (++c_k == KT) {
@@ -832,85 +876,101 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
         c_n = min(c_n + 1, n1 - 1);
         const Item it = item(c_n);
         w_base = w_of(it);
-        a_base = a_of(it) + wave * 2048;
+        a_base = a_of(it) + wave * (ALL_A ? 4096 : 2048);
         a_step = it.live * 4096;
-        a_b = __builtin_amdgcn_readfirstlane((wave >> 1) < it.live ? 1 : 0);
+        a_b = __builtin_amdgcn_readfirstlane((ALL_A ? wave : wave >> 1) < it.live ? 1 : 0);
         if (F8) s_ptr = s_of(it);
       }
-      dst = ring_lds + c_s * SLOT;
+      const uint32_t st = ring_lds + c_s * SLOT;
+      a_dst = st + wave * (ALL_A ? 4096 : 2048);
+      w_dst = st + AB + wave * (HALF ? 2048 : 4096);
       s_dst = ring_lds + WT_S + c_s * WT_SC + wave * WT_SCW;
       w_src = w_base + (size_t)c_k * B_BYTES;
       a_src = a_base + (size_t)c_k * a_step;
     };
-    auto put_w = [&](int q) {
-      if (q == 0) lds_dma16s_at<0>(w_src, lane16, dst + AB + wave * 4096);
-      if (q == 1) lds_dma16s_at<1>(w_src, lane16, dst + AB + wave * 4096);
-      if (q == 2) lds_dma16s_at<2>(w_src, lane16, dst + AB + wave * 4096);
-      if (q == 3) lds_dma16s_at<3>(w_src, lane16, dst + AB + wave * 4096);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    auto put_sa = [&](int q) {
-      if (F8 && q == 0) {
+    // the loads of a step, one after a quarter of a row block's MFMAs each
+    auto put = [&](int q) {
+      if (q == 0) lds_dma16s_at<0>(w_src, lane16, w_dst);
+      if (q == 1) lds_dma16s_at<1>(w_src, lane16, w_dst);
+      if (!HALF && q == 2) lds_dma16s_at<2>(w_src, lane16, w_dst);
+      if (!HALF && q == 3) lds_dma16s_at<3>(w_src, lane16, w_dst);
+      if (F8 && q == 4) {
         lds_dma16v_lanes(s_ptr, s_dst, S_LANES);
         s_ptr += lane < 8 ? a_step / 32 : 16;
       }
-      if (q == 1) lds_dma16s_x2_if(a_src, lane16, dst + wave * 2048, a_b);
+      if (q == 5) lds_dma16s_x2_if(a_src, lane16, a_dst, a_b);
+      if (ALL_A && q == 6) lds_dma16s_x2_if(a_src + 2048, lane16, a_dst + 2048, a_b);
       __builtin_amdgcn_sched_barrier(0);
     };
-    auto all = [&](auto put) {
+    auto put_lo = [&](int q) { put(q); };
+    auto put_hi = [&](int q) { put(4 + q); };
+    auto all = [&](auto f) {
 #pragma unroll
-      for (int q = 0; q < 4; q++) put(q);
+      for (int q = 0; q < 4; q++) f(q);
     };
     constexpr std::integral_constant<int, (NSL - 2) * L> in_flight{};
-#pragma unroll
+    static_assert((NSL - 2) * L <= 63, "the vmcnt field");
+#pragma unroll 1
     for (int i = 0; i < NSL - 1; i++) {
       next();
-      all(put_w);
-      all(put_sa);
+      all(put_lo);
+      all(put_hi);
     }
     sync(in_flight);
     int rd = 0;
 #pragma unroll 1
     for (int n = n0; n < n1; n++) {
-      const Out o = begin(std::integral_constant<int, 2>{}, n);
+      const Out o = begin(ni, n);
       const int nb = o.nb;
 #pragma unroll 1
       for (int k = 0; k < KT; k++) {
-        const char* st = ring + rd * SLOT;
+        const char* const sa_at = ring + rd * SLOT + (HALF ? wave >> 1 : wm) * 4096;
+        const char* const sw_at = ring + rd * SLOT + AB + (HALF ? wave & 1 : wn) * 8192;
         if (0 < nb) {
-          read_b(st + AB, 0);
-          read_a(st, 0);
-          read_b(st + AB, 1);
-          if (F8) read_s(rd);
-          if (1 < nb) read_a(st, 1);
+          read_b(sw_at, 0);
+          read_a(sa_at, 0);
+          read_b(sw_at, 1);
+          if (F8) read_s(ni, rd, HALF ? wave >> 1 : wm, HALF ? 4 : 2, HALF ? 0 : wn >> 1);
+          if (NI > 1 && 1 < nb) read_a(sa_at + (HALF ? 4 : 2) * 4096, 1);
         }
         __builtin_amdgcn_sched_barrier(0);
         next();
-        if (0 < nb) mul(0, put_w);
-        else all(put_w);
-        if (1 < nb) mul(1, put_sa);
-        else all(put_sa);
+        if (0 < nb) mul(0, put_lo);
+        else all(put_lo);
+        if (NI > 1 && 1 < nb) mul(1, put_hi);
+        else all(put_hi);
         // step k + 1 has landed and everyone is done with this one's slot
         sync(in_flight);
         if (++rd == NSL) rd = 0;
       }
-      finish(std::integral_constant<int, 2>{}, o);
+      finish(ni, o);
     }
   };
 
-  // the items in runs of one kind (at most three, as the order is sorted)
+  // the items in runs of one kind (a few, as the order is sorted)
   auto kind = [&](int n) {
-    const int live = sorted ? item(n).live : 8;
-    return live > 4 ? 0 : live > 1 ? 1 : 2;
+    const Item it = item(n);
+    const int live = sorted ? it.live : 8;
+    return (it.half < 0 ? 0 : 3) + (live > 4 ? 0 : live > 1 ? 1 : 2);
   };
 #pragma unroll 1
   for (int n0 = 0; n0 < my_items;) {
     const int kd = kind(n0);
     int n1 = n0 + 1;
     while (n1 < my_items && kind(n1) == kd) n1++;
+    constexpr std::false_type whole{};
+    constexpr std::true_type half{};
+    constexpr std::integral_constant<int, 4096> a1{};
+    constexpr std::integral_constant<int, WT_UNIT> a4{};
+    constexpr std::integral_constant<int, WT_STEP> a8{};
     if (kd == 0) run_wide(n0, n1);
-    else if (kd == 1) run_narrow(n0, n1, std::integral_constant<int, 3>{});
-    else run_narrow(n0, n1, std::integral_constant<int, 4>{});
+    else if (kd == 1) run_small(n0, n1, whole, std::integral_constant<int, 3>{}, a4);
+    else if (!HALVES || kd == 2) run_small(n0, n1, whole, std::integral_constant<int, 4>{}, a1);
+    else if constexpr (HALVES) {
+      if (kd == 3) run_small(n0, n1, half, std::integral_constant<int, 3>{}, a8);
+      else if (kd == 4) run_small(n0, n1, half, std::integral_constant<int, 4>{}, a4);
+      else run_small(n0, n1, half, std::integral_constant<int, 7>{}, a1);
+    }
     n0 = n1;
     // no DMA of one run may land in the next one's ring, or outlive the workgroup
     sync(std::integral_constant<int, 0>{});
@@ -987,29 +1047,45 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 // the chip.  The counts per slot are only known on the device; rows per
 // expert, T K / E, and the items that these make, stand for them (the same
 // for every plan, so a row's result does not depend on it).
-// Measured, forward us, other kernel -> wide tiles (uniform plans; 18 slots H
-// 4096 I 1536 unless 36 slots H 7168 I 2048 or 10 slots H 2048 I 1408 is said):
-//   fp8    rows per expert 8: 103 -> 100 (36 slots 323 -> 326), 16: 129 -> 112
-//          (36 slots 389 -> 380), 32: 149 -> 127, 64: 181 -> 137, 128: 252 ->
-//          164, 512: 710 -> 368; items 30: 78 -> 95, 67: 102 -> 101, 114: 71
-//          -> 72, 139: 100 -> 87
-//   UE8M0  16: 119 -> 112 (36 slots 371 -> 376), 32: 142 -> 125 (36 slots 488
-//          -> 408), 64: 164 -> 133, 128: 219 -> 164; short contractions
-//          (H 1152): 32: 68 -> 72, 96: 81 -> 74; items 73: 94 -> 91; against its
-//          own 256-row kernel 160: 173 -> 173, 512: 327 -> 333
-//   bf16   16: 178 -> 179, 32: 208 -> 202 (with a plan that leaves one slot
-//          of six live row blocks, 181 -> 191; 36 slots 854 -> 735), 64: 249 ->
-//          208 (36 slots with 128-row tiles 651 -> 669), 92: 305 -> 228, 187:
-//          316 -> 247, 512: 593 -> 551; items 133: 175 -> 191, 192 (10 slots):
-//          126 -> 138, 275 (10 slots): 160 -> 153
+// Which of two kernels wins near the line depends on the plan: uniform shares
+// leave slots of very different sizes, which the other kernel balances worst;
+// a plan that keeps few replicas busy leaves it slots of few rows each, its
+// best case.  Measured, forward us, other kernel -> wide tiles, uniform plan /
+// token balancing / fewest replicas (18 slots H 4096 I 1536; "36": 36 slots
+// H 7168 I 2048; "10": 10 slots H 2048 I 1408; "5" etc.: that many slots):
+//   bf16   64-row tiles, rows per expert 32: 203 -> 193 / 179 -> 191 / 147 ->
+//          160; 48: 218 -> 201 / 199 -> 195 / 159 -> 173 (36: 1048 -> 738 /
+//          826 -> 676 / 679 -> 653); 64: 241 -> 207 / 224 -> 203 / 183 -> 176.
+//          128-row tiles, 64: 221 -> 209 / 211 -> 203 / 187 -> 178 (36: 1038 ->
+//          767 / 828 -> 689 / 698 -> 660).  256-row tiles, 32: 232 -> 192 /
+//          228 -> 188 / 186 -> 164; 512: 593 -> 546.  Items 121 (10): 87 -> 86
+//          / 80 -> 86 / 58 -> 70; 143 (10): 110 -> 93 / 98 -> 91 / 77 -> 87;
+//          with 256-row tiles 66: 46 -> 53, 80: 98 -> 75 (5) and 86 -> 70 (10),
+//          121: 107 -> 86 / 108 -> 86 / 104 -> 72
+//   fp8    rows 8: 103 -> 100 (36: 323 -> 326); 12: - / 109 -> 103 / 105 -> 94
+//          (36: - / 316 -> 321 / 291 -> 280); 16: 129 -> 112 / 119 -> 110 / 110
+//          -> 98 (36: 389 -> 380 / 329 -> 348 / 306 -> 298); 32: 149 -> 132 /
+//          129 -> 127 / 115 -> 123 (36: 499 -> 426 / 418 -> 410 / 358 -> 346);
+//          128: 252 -> 164; 512: 710 -> 368.  Items 66: 53 -> 53, 80 of 256 rows
+//          (5): 69 -> 74, 110 of 256 rows (5): 72 -> 75, 121 (10): 79 -> 74 /
+//          73 -> 74 / 57 -> 60, 132 (10): 97 -> 82 / 86 -> 80 / 74 -> 72, 143
+//          (10): 106 -> 83 / 94 -> 83 / 77 -> 77
+//   UE8M0  rows 24: - / 115 -> 121 / 99 -> 100; 40: 144 -> 132 / 129 -> 129 /
+//          107 -> 118; 64: 159 -> 137 / 150 -> 134 / 125 -> 127; 36 slots 24: - /
+//          367 -> 385 / 315 -> 324, 32: 480 -> 414 / 399 -> 404 / 338 -> 335, 48:
+//          591 -> 441 / 471 -> 414 / 391 -> 390.  Items 132 (10): 84 -> 77 / 75
+//          -> 77 / 64 -> 69; with 256-row tiles 110 (5): 91 -> 71; short
+//          contractions (H 1152): 32: 68 -> 72, 96: 81 -> 74; against its own
+//          256-row kernel 160: 173 -> 173, 512: 327 -> 333
 bool experts_wide_wanted(const tempo_moe_shape& s) {
   if (experts_big_f8_supported(s)) return false;
   const long long P = (long long)s.T * s.K, E = s.E;
   // items of the gate/up GEMM, were the pairs spread evenly over the experts
   const long long items = (s.S + P * s.S / (256 * E)) * (s.I / 128);
-  if (s.dtype == TEMPO_BF16) return items >= 200 && P >= (s.m_tile == 64 ? 48 : 80) * E;
-  if (s.dtype == TEMPO_FP8_E4M3) return items >= 80 && P >= 12 * E;
-  return items >= 80 && P >= (s.H >= 2048 ? 24 : 64) * E;
+  const bool m256 = s.m_tile == 256;
+  if (s.dtype == TEMPO_BF16) return items >= (m256 ? 80 : 150) && P >= (m256 ? 32 : s.m_tile == 64 ? 48 : 64) * E;
+  if (s.dtype == TEMPO_FP8_E4M3) return items >= (m256 ? 80 : 130) && P >= 12 * E;
+  return items >= (m256 ? 80 : 150) && P >= (items >= 500 ? 32 : 56) * E;
 }
 
 hipError_t launch_experts_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,

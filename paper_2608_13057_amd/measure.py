@@ -43,7 +43,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 COPY_BYTES = 256 << 20
 GEMM_SOURCES = ("gemm_stream.h", "gemm_common.h", "gemm_bf16.hip", "gemm_fp8.hip", "gemm_big_agpr.hip", "gemm_big_f8_agpr.hip",
-                "pack.hip")
+                "gemm_wide.hip", "pack.hip")
 
 
 def gemm_source_hash() -> str:
@@ -68,15 +68,31 @@ def auto_m_tile(wl) -> int:
 
 
 def uses_big_kernel(dtype: str, m_tile: int, H: int, I: int = 256) -> bool:
-    """Whether stage 2 runs a 256 x 256-item large-tile GEMM (bf16, or UE8M0
+    """Whether the tiles allow a 256 x 256-item large-tile GEMM (bf16, or UE8M0
     fp8 with I a multiple of 256, with 256-row tiles and H a multiple of 256)
     rather than the stream-K one."""
     return (dtype == "bf16" or (dtype == "fp8mx" and I % 256 == 0)) and m_tile == 256 and H % 256 == 0
 
 
-def gateup_kernel_name(dtype: str, m_tile: int, H: int, I: int = 256) -> str:
+def uses_wide_kernel(wl, m_tile: int) -> bool:
+    """Whether stage 2 runs the wide-tile GEMMs: the rule of
+    experts_wide_wanted (csrc/gemm_wide.hip) on a workload's sizes."""
+    if wl.dtype == "fp8mx" and uses_big_kernel(wl.dtype, m_tile, wl.H, wl.I):
+        return False
+    P, m256 = wl.T * wl.K, m_tile == 256
+    items = (wl.S + P * wl.S // (256 * wl.E)) * (wl.I // 128)
+    if wl.dtype == "bf16":
+        return items >= (80 if m256 else 150) and P >= (32 if m256 else 48 if m_tile == 64 else 64) * wl.E
+    if wl.dtype == "fp8":
+        return items >= (80 if m256 else 130) and P >= 12 * wl.E
+    return items >= (80 if m256 else 150) and P >= (32 if items >= 500 else 56) * wl.E
+
+
+def gateup_kernel_name(dtype: str, m_tile: int, H: int, I: int = 256, wide: bool = False) -> str:
     """Symbol (as rocprofv3 prints it) of the gate/up GEMM kernel a forward
     launches."""
+    if wide:
+        return f"tempo::(anonymous namespace)::k_gemm_wide<{('fp8', 'fp8mx', 'bf16').index(dtype)}, true>"
     if uses_big_kernel(dtype, m_tile, H, I):
         return ("tempo::(anonymous namespace)::k_gemm_big<true>" if dtype == "bf16" else
                 "tempo::(anonymous namespace)::k_gemm_big_f8<true>")
@@ -188,10 +204,14 @@ def _mean_counter(rows, counter: str, match):
 
 
 def _is_gateup(name: str) -> bool:
-    """The gate/up GEMM: the large-tile kernel k_gemm_big<true>, or the
-    stream-K instance with GATEUP (its third template argument)."""
-    if "k_gemm_big<true>" in name.replace(" ", "") or "k_gemm_big_f8<true>" in name.replace(" ", ""):
+    """The gate/up GEMM: the large-tile kernel k_gemm_big<true>, the wide-tile
+    one with GATEUP (its second template argument), or the stream-K instance
+    with it (its third)."""
+    flat = name.replace(" ", "")
+    if "k_gemm_big<true>" in flat or "k_gemm_big_f8<true>" in flat:
         return True
+    if "k_gemm_wide<" in flat:
+        return flat.split("k_gemm_wide<", 1)[1].split(">", 1)[0].split(",")[1] == "true"
     if "k_gemm<" not in name:
         return False
     args = name.replace(" ", "").split("k_gemm<", 1)[1].split(">", 1)[0].split(",")

@@ -283,13 +283,15 @@ def test_forward_256_row_tiles_random_shapes(dtype, seed):
 
 @pytest.mark.parametrize("dtype,m_tile,H,reps", [("fp8", 64, 128, 1), ("fp8", 128, 384, 2), ("fp8", 256, 640, 1),
                                                  ("fp8mx", 64, 384, 2), ("fp8mx", 256, 128, 1),
-                                                 ("bf16", 64, 128, 1), ("bf16", 128, 384, 2), ("bf16", 256, 384, 1)])
+                                                 ("bf16", 64, 128, 1), ("bf16", 128, 384, 2), ("bf16", 256, 384, 1),
+                                                 ("fp8", 64, 640, 4), ("fp8mx", 128, 640, 4), ("bf16", 64, 640, 4)])
 def test_forward_wide_tiles(dtype, m_tile, H, reps):
     """The wide-tile kernels at their edges: slots of no row, of every number
     of live 32-row blocks of a 256-row tile, one row past a tile, and of two
     to four tiles; contractions of one step (H 128, fp8) up; an odd number of
-    128-row weight blocks in the down GEMM; one or (reps 2) several items per
-    workgroup; stage 1 in every M-tile.  y on a token sample (one row of every
+    128-row weight blocks in the down GEMM; a round of half items only (reps 1
+    and 2; for fp8 gate/up whole ones) or whole items first (reps 4, also in
+    the down GEMM); stage 1 in every M-tile.  y on a token sample (one row of every
     M-tile, every slot's last row, 200 random tokens) against the fp64 oracle
     in exact and mirror modes; tokens with no local pair exactly zero; the
     plain call of the three stages gives the same bits as the forward."""
