@@ -351,10 +351,14 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
   const int items = NT * NBT;
   const int G = gridDim.x;
   const int lin0 = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
-  // `full` whole rounds of items, then what is left in halves
+  // `full` whole rounds of items, then what is left in halves; where there is
+  // no whole round, only what fits one round of halves (two of them take
+  // longer than one of whole items: 10 slots, 3377 tokens, bf16 146 us for
+  // 134 on 230 gate/up items)
   const int full = items / G;
   int rest = items - full * G, rounds = full;
-  if (HALVES) {
+  const bool halve = HALVES && (full > 0 || 2 * rest <= G);
+  if (halve) {
     rest *= 2;
     if (rest >= G) rest -= G, rounds++;
   }
@@ -368,7 +372,7 @@ __global__ __launch_bounds__(WT_THREADS, 2) void k_gemm_wide(const WideArgs p) {
     if (blockIdx.x & 1) n = my_items - 1 - n;
     int it = n * G + ((n & 1) ? G - 1 - lin0 : lin0);
     half = -1;
-    if (HALVES && n >= full) {
+    if (halve && n >= full) {
       const int j = it - full * G;
       it = full * G + (j >> 1);
       half = j & 1;
@@ -1057,24 +1061,30 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 //          160; 48: 218 -> 201 / 199 -> 195 / 159 -> 173 (36: 1048 -> 738 /
 //          826 -> 676 / 679 -> 653); 64: 241 -> 207 / 224 -> 203 / 183 -> 176.
 //          128-row tiles, 64: 221 -> 209 / 211 -> 203 / 187 -> 178 (36: 1038 ->
-//          767 / 828 -> 689 / 698 -> 660).  256-row tiles, 32: 232 -> 192 /
-//          228 -> 188 / 186 -> 164; 512: 593 -> 546.  Items 121 (10): 87 -> 86
-//          / 80 -> 86 / 58 -> 70; 143 (10): 110 -> 93 / 98 -> 91 / 77 -> 87;
-//          with 256-row tiles 66: 46 -> 53, 80: 98 -> 75 (5) and 86 -> 70 (10),
-//          121: 107 -> 86 / 108 -> 86 / 104 -> 72
+//          767 / 828 -> 689 / 698 -> 660; 48: 882 -> 735).  Many items (36), 32:
+//          841 -> 694 / 696 -> 671 / 578 -> 597.  Items 121 (10): 87 -> 86
+//          / 80 -> 86 / 58 -> 70; 143 (10): 110 -> 93 / 98 -> 91 / 77 -> 87.
+//          256-row tiles, 24: 222 -> 185 / - / 183 -> 155; 32: 232 -> 192 / 228
+//          -> 188 / 186 -> 164; 512: 593 -> 546; items 6 (2): 96 -> 71, 42 (5):
+//          92 -> 73, 84 (5): 111 -> 89.  But full tiles that make about one
+//          round of items, the other large-tile kernel's best case: items 144:
+//          135 -> 139, 192: 155 -> 165, 242: 137 -> 142, 264: 141 -> 145; then
+//          312: 266 -> 236, 341: 201 -> 183, 444: 400 -> 355
 //   fp8    rows 8: 103 -> 100 (36: 323 -> 326); 12: - / 109 -> 103 / 105 -> 94
 //          (36: - / 316 -> 321 / 291 -> 280); 16: 129 -> 112 / 119 -> 110 / 110
 //          -> 98 (36: 389 -> 380 / 329 -> 348 / 306 -> 298); 32: 149 -> 132 /
 //          129 -> 127 / 115 -> 123 (36: 499 -> 426 / 418 -> 410 / 358 -> 346);
 //          128: 252 -> 164; 512: 710 -> 368.  Items 66: 53 -> 53, 80 of 256 rows
-//          (5): 69 -> 74, 110 of 256 rows (5): 72 -> 75, 121 (10): 79 -> 74 /
+//          (5): 69 -> 74, 110 of 256 rows (5): 72 -> 75 (with 256-row M-tiles 9
+//          (2): 97 -> 75, 44 (3): 104 -> 96), 121 (10): 79 -> 74 /
 //          73 -> 74 / 57 -> 60, 132 (10): 97 -> 82 / 86 -> 80 / 74 -> 72, 143
 //          (10): 106 -> 83 / 94 -> 83 / 77 -> 77
 //   UE8M0  rows 24: - / 115 -> 121 / 99 -> 100; 40: 144 -> 132 / 129 -> 129 /
 //          107 -> 118; 64: 159 -> 137 / 150 -> 134 / 125 -> 127; 36 slots 24: - /
 //          367 -> 385 / 315 -> 324, 32: 480 -> 414 / 399 -> 404 / 338 -> 335, 48:
 //          591 -> 441 / 471 -> 414 / 391 -> 390.  Items 132 (10): 84 -> 77 / 75
-//          -> 77 / 64 -> 69; with 256-row tiles 110 (5): 91 -> 71; short
+//          -> 77 / 64 -> 69; with 256-row tiles 9 (2): 84 -> 71, 44 (3): 88 ->
+//          87, 110 (5): 91 -> 71 and 121 at 36 rows: 81 -> 71; short
 //          contractions (H 1152): 32: 68 -> 72, 96: 81 -> 74; against its own
 //          256-row kernel 160: 173 -> 173, 512: 327 -> 333
 bool experts_wide_wanted(const tempo_moe_shape& s) {
@@ -1082,10 +1092,13 @@ bool experts_wide_wanted(const tempo_moe_shape& s) {
   const long long P = (long long)s.T * s.K, E = s.E;
   // items of the gate/up GEMM, were the pairs spread evenly over the experts
   const long long items = (s.S + P * s.S / (256 * E)) * (s.I / 128);
-  const bool m256 = s.m_tile == 256;
-  if (s.dtype == TEMPO_BF16) return items >= (m256 ? 80 : 150) && P >= (m256 ? 32 : s.m_tile == 64 ? 48 : 64) * E;
-  if (s.dtype == TEMPO_FP8_E4M3) return items >= (m256 ? 80 : 130) && P >= 12 * E;
-  return items >= (m256 ? 80 : 150) && P >= (items >= 500 ? 32 : 56) * E;
+  const bool m256 = s.m_tile == 256, many = items >= 500;
+  if (s.dtype == TEMPO_BF16) {
+    if (m256) return P >= 24 * E && !(s.H % 256 == 0 && P >= 256 * E && items > 128 && items <= 270);
+    return items >= 150 && P >= (s.m_tile == 64 ? (many ? 32 : 48) : (many ? 48 : 64)) * E;
+  }
+  if (s.dtype == TEMPO_FP8_E4M3) return (m256 || items >= 130) && P >= 12 * E;
+  return (m256 || items >= 150) && P >= (m256 || many ? 32 : 56) * E;
 }
 
 hipError_t launch_experts_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,

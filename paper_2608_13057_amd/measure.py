@@ -79,13 +79,16 @@ def uses_wide_kernel(wl, m_tile: int) -> bool:
     experts_wide_wanted (csrc/gemm_wide.hip) on a workload's sizes."""
     if wl.dtype == "fp8mx" and uses_big_kernel(wl.dtype, m_tile, wl.H, wl.I):
         return False
-    P, m256 = wl.T * wl.K, m_tile == 256
-    items = (wl.S + P * wl.S // (256 * wl.E)) * (wl.I // 128)
+    P, E, m256 = wl.T * wl.K, wl.E, m_tile == 256
+    items = (wl.S + P * wl.S // (256 * E)) * (wl.I // 128)
+    many = items >= 500
     if wl.dtype == "bf16":
-        return items >= (80 if m256 else 150) and P >= (32 if m256 else 48 if m_tile == 64 else 64) * wl.E
+        if m256:
+            return P >= 24 * E and not (wl.H % 256 == 0 and P >= 256 * E and 128 < items <= 270)
+        return items >= 150 and P >= ((32 if many else 48) if m_tile == 64 else (48 if many else 64)) * E
     if wl.dtype == "fp8":
-        return items >= (80 if m256 else 130) and P >= 12 * wl.E
-    return items >= (80 if m256 else 150) and P >= (32 if items >= 500 else 56) * wl.E
+        return (m256 or items >= 130) and P >= 12 * E
+    return (m256 or items >= 150) and P >= (32 if m256 or many else 56) * E
 
 
 def gateup_kernel_name(dtype: str, m_tile: int, H: int, I: int = 256, wide: bool = False) -> str:
