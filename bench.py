@@ -315,12 +315,12 @@ def roofline(m, copy_gbs=None):
     when the path runs the large-tile kernel or most pairs sit in slots past
     the MFMA/HBM balance point, otherwise HBM-bound (weights of the G
     activated slots once + the N real activation rows in and h rows out)."""
-    from paper_2608_13057_amd import measure
+    from paper_2608_13057_amd import measure, moe
 
     wl = m.wl
     gu_s = m.kernel_us["gate_up_gemm"] * 1e-6
-    wide = measure.uses_wide_kernel(wl, m.m_tile)
-    kernel = measure.gateup_kernel_name(wl.dtype, m.m_tile, wl.H, wl.I, wide)
+    shape = moe.MoEShape(T=wl.T, K=wl.K, E=wl.E, S=wl.S, H=wl.H, I=wl.I, m_tile=m.m_tile, dtype=wl.dtype)
+    kernel = measure.gateup_kernel_name(shape)
     traffic, traffic_current = measure.committed_traffic(m.name, m.m_tile)
     common = {"traffic": traffic if traffic_current else None, "kernel": kernel + " (gate/up)",
               "launch_us": m.kernel_us["gate_up_gemm"], "G": m.G, "N": m.N}
@@ -328,7 +328,7 @@ def roofline(m, copy_gbs=None):
     if mf is not None:  # counter evidence (rocprofv3 --pmc) for the same kernel sources
         common["mfma_counters"] = {k: mf[k] for k in ("mfma_busy", "clock_ghz", "executed_tflops", "launch_us")}
     # pairs per activated slot against the ideal balance point e P / (2 BW) ~ 312
-    linear = measure.uses_big_kernel(wl.dtype, m.m_tile, wl.H, wl.I) or m.N / max(1, m.G) > 312
+    linear = (m.m_tile == 256 and measure.stage2_route(shape) != "stream") or m.N / max(1, m.G) > 312
     if linear:
         fl = gemm_flops(wl, m.N, "gateup")
         peak = MFMA_PEAK_TFLOPS[wl.dtype]

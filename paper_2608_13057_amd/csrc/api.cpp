@@ -147,6 +147,14 @@ int tempo_moe_query(const tempo_moe_shape* shape, size_t* workspace_bytes, int32
   return TEMPO_OK;
 }
 
+int tempo_internal_stage2_route(const tempo_moe_shape* shape) {
+  if (check_shape(shape)) return -1;
+  // (in the order in which launch_experts_bf16 / _fp8 ask)
+  if (make_layout(*shape).wide_tiles) return kRouteWide;
+  if (experts_big_f8_supported(*shape)) return kRouteBigF8;
+  return experts_big_supported(*shape) ? kRouteBig : kRouteStream;
+}
+
 int tempo_moe_counter_window(int32_t E, const uint32_t* before, const uint32_t* after, uint32_t* window) {
   if (E < 1 || !before || !after || !window) return TEMPO_EINVAL;
   for (int32_t e = 0; e < E; e++) window[e] = after[e] - before[e];  // unsigned: modulo 2^32

@@ -131,6 +131,14 @@ bool experts_gather_rows(const tempo_moe_shape& s, const Layout& L);
 bool stream_gathers_rows(const tempo_moe_shape& s, const Layout& L);
 bool experts_reads_token_scales(const tempo_moe_shape& s, const Layout& L);
 
+// Kernel family that stage 2 of a shape runs on (tempo_internal_stage2_route).
+enum Stage2Route : int {
+  kRouteStream = 0,  // k_gemm (stream-K)
+  kRouteBig = 1,     // k_gemm_big
+  kRouteBigF8 = 2,   // k_gemm_big_f8
+  kRouteWide = 3,    // k_gemm_wide
+};
+
 // Whether stage-2 kernels exist for this shape's element type and M-tile.
 bool experts_supported(const tempo_moe_shape& s);
 
@@ -139,3 +147,7 @@ bool experts_supported(const tempo_moe_shape& s);
 int persistent_grid(int per_cu);
 
 }  // namespace tempo
+
+// Host only, for the measurement tools and the tests (not part of the public
+// ABI): the Stage2Route of a shape, or -1 for one that the library rejects.
+extern "C" int tempo_internal_stage2_route(const tempo_moe_shape* shape);

@@ -67,41 +67,35 @@ def auto_m_tile(wl) -> int:
     return 256
 
 
-def uses_big_kernel(dtype: str, m_tile: int, H: int, I: int = 256) -> bool:
-    """Whether the tiles allow a 256 x 256-item large-tile GEMM (bf16, or UE8M0
-    fp8 with I a multiple of 256, with 256-row tiles and H a multiple of 256)
-    rather than the stream-K one."""
-    return (dtype == "bf16" or (dtype == "fp8mx" and I % 256 == 0)) and m_tile == 256 and H % 256 == 0
+ROUTES = ("stream", "big", "big_f8", "wide")
 
 
-def uses_wide_kernel(wl, m_tile: int) -> bool:
-    """Whether stage 2 runs the wide-tile GEMMs: the rule of
-    experts_wide_wanted (csrc/gemm_wide.hip) on a workload's sizes."""
-    if wl.dtype == "fp8mx" and uses_big_kernel(wl.dtype, m_tile, wl.H, wl.I):
-        return False
-    P, E, m256 = wl.T * wl.K, wl.E, m_tile == 256
-    items = (wl.S + P * wl.S // (256 * E)) * (wl.I // 128)
-    many = items >= 500
-    if wl.dtype == "bf16":
-        if m256:
-            return P >= 24 * E and not (wl.H % 256 == 0 and P >= 256 * E and 128 < items <= 270)
-        return items >= 150 and P >= ((32 if many else 48) if m_tile == 64 else (48 if many else 64)) * E
-    if wl.dtype == "fp8":
-        return (m256 or items >= 130) and P >= 12 * E
-    return (m256 or items >= 150) and P >= (32 if m256 or many else 56) * E
+def stage2_route(shape) -> str:
+    """The kernel family stage 2 of a moe.MoEShape runs on, as the library
+    chooses it from the shape: "stream" (stream-K), "big" / "big_f8" (256-row
+    large tiles, bf16 / UE8M0 fp8) or "wide" (wide tiles)."""
+    import ctypes
+
+    from . import _lib
+
+    sh = shape.c()
+    r = _lib.load().tempo_internal_stage2_route(ctypes.byref(sh))
+    if r < 0:
+        raise ValueError(f"the library rejects {shape}")
+    return ROUTES[r]
 
 
-def gateup_kernel_name(dtype: str, m_tile: int, H: int, I: int = 256, wide: bool = False) -> str:
-    """Symbol (as rocprofv3 prints it) of the gate/up GEMM kernel a forward
-    launches."""
-    if wide:
-        return f"tempo::(anonymous namespace)::k_gemm_wide<{('fp8', 'fp8mx', 'bf16').index(dtype)}, true>"
-    if uses_big_kernel(dtype, m_tile, H, I):
-        return ("tempo::(anonymous namespace)::k_gemm_big<true>" if dtype == "bf16" else
-                "tempo::(anonymous namespace)::k_gemm_big_f8<true>")
-    fp8 = "false" if dtype == "bf16" else "true"
-    mx = "true" if dtype == "fp8mx" else "false"
-    return f"tempo::gemm::k_gemm<{fp8}, {m_tile}, true, {mx}>"
+def gateup_kernel_name(shape) -> str:
+    """Symbol (as rocprofv3 prints it) of the gate/up GEMM kernel a forward of
+    a moe.MoEShape launches."""
+    route = stage2_route(shape)
+    if route == "wide":
+        return f"tempo::(anonymous namespace)::k_gemm_wide<{('fp8', 'fp8mx', 'bf16').index(shape.dtype)}, true>"
+    if route != "stream":
+        return f"tempo::(anonymous namespace)::k_gemm_{route}<true>"
+    fp8 = "false" if shape.dtype == "bf16" else "true"
+    mx = "true" if shape.dtype == "fp8mx" else "false"
+    return f"tempo::gemm::k_gemm<{fp8}, {shape.m_tile}, true, {mx}>"
 
 
 def traffic_path(workload: str, m_tile: int) -> str:

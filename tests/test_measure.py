@@ -7,7 +7,7 @@ import os
 
 import pytest
 
-from paper_2608_13057_amd import measure
+from paper_2608_13057_amd import measure, moe
 
 GU = "void tempo::(anonymous namespace)::k_gemm_big_f8<true>(tempo::(anonymous namespace)::F8Args)"
 COPY = "void at::native::vectorized_elementwise_kernel<4, at::native::AUnaryFunctor<float, float, float, " \
@@ -37,7 +37,31 @@ def test_kernel_classification():
     assert not measure._is_gateup("void tempo::(anonymous namespace)::k_gemm_big<false>(tempo::gemm::GemmArgs)")
     assert measure._is_gateup("void tempo::gemm::k_gemm<false, 64, true, false>(tempo::gemm::GemmArgs)")
     assert not measure._is_gateup("void tempo::gemm::k_gemm<false, 64, false, false>(tempo::gemm::GemmArgs)")
+    for t in (0, 1, 2):
+        w = "void tempo::(anonymous namespace)::k_gemm_wide<%d, %s>(tempo::(anonymous namespace)::WideArgs)"
+        assert measure._is_gateup(w % (t, "true")) and not measure._is_gateup(w % (t, "false"))
     assert measure._is_copy(COPY) and not measure._is_copy(GU)
+
+
+@pytest.mark.parametrize("dtype,T,S,H,I,m_tile,route,name", [
+    ("bf16", 512, 18, 4096, 1536, 64, "stream", "k_gemm<false, 64, true, false>"),
+    ("fp8", 64, 18, 4096, 1536, 256, "stream", "k_gemm<true, 256, true, false>"),
+    ("fp8mx", 64, 18, 4096, 1408, 256, "stream", "k_gemm<true, 256, true, true>"),
+    ("bf16", 64, 18, 4096, 1536, 256, "big", "k_gemm_big<true>"),
+    ("fp8mx", 8192, 18, 4096, 1536, 256, "big_f8", "k_gemm_big_f8<true>"),
+    ("bf16", 8192, 18, 4096, 1536, 256, "wide", "k_gemm_wide<2, true>"),
+    ("fp8", 8192, 18, 4096, 1536, 128, "wide", "k_gemm_wide<0, true>"),
+    ("fp8mx", 8192, 18, 4096, 1536, 128, "wide", "k_gemm_wide<1, true>")])
+def test_kernel_name_is_the_librarys_choice(dtype, T, S, H, I, m_tile, route, name):
+    """The benchmark line names the kernel that the library itself says it
+    launches for the shape (one rule, asked for, not written twice), and the
+    counter summaries recognise that name."""
+    shape = moe.MoEShape(T=T, K=8, E=128, S=S, H=H, I=I, m_tile=m_tile, dtype=dtype)
+    assert measure.stage2_route(shape) == route
+    full = measure.gateup_kernel_name(shape)
+    assert full.endswith("::" + name) and measure._is_gateup(full)
+    with pytest.raises(ValueError):
+        measure.stage2_route(moe.MoEShape(T=T, K=8, E=128, S=S, H=H, I=I, m_tile=96, dtype=dtype))
 
 
 def test_mfma_summary_arithmetic(tmp_path):
