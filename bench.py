@@ -328,7 +328,7 @@ def roofline(m, copy_gbs=None):
     if mf is not None:  # counter evidence (rocprofv3 --pmc) for the same kernel sources
         common["mfma_counters"] = {k: mf[k] for k in ("mfma_busy", "clock_ghz", "executed_tflops", "launch_us")}
     # pairs per activated slot against the ideal balance point e P / (2 BW) ~ 312
-    linear = (m.m_tile == 256 and measure.stage2_route(shape) != "stream") or m.N / max(1, m.G) > 312
+    linear = (m.m_tile == 256 and not measure.stage2_route(shape).startswith("stream")) or m.N / max(1, m.G) > 312
     if linear:
         fl = gemm_flops(wl, m.N, "gateup")
         peak = MFMA_PEAK_TFLOPS[wl.dtype]

@@ -152,7 +152,8 @@ int tempo_internal_stage2_route(const tempo_moe_shape* shape) {
   // (in the order in which launch_experts_bf16 / _fp8 ask)
   if (make_layout(*shape).wide_tiles) return kRouteWide;
   if (experts_big_f8_supported(*shape)) return kRouteBigF8;
-  return experts_big_supported(*shape) ? kRouteBig : kRouteStream;
+  if (experts_big_supported(*shape)) return kRouteBig;
+  return stream_whole_items(*shape) ? kRouteStream : kRouteStreamSplit;
 }
 
 int tempo_moe_counter_window(int32_t E, const uint32_t* before, const uint32_t* after, uint32_t* window) {

@@ -1,6 +1,8 @@
 // Stage 2, bf16: the stream-K grouped GEMM of gemm_stream.h with bf16
 // operands and fp32 accumulation; h is rounded to bf16 (round to nearest
 // even) after SwiGLU, y_perm to bf16 after the down projection.
+#include <cmath>
+
 #include "gemm_stream.h"
 
 namespace tempo {
@@ -38,13 +40,14 @@ hipError_t launch_bm(const tempo_moe_shape& s, const tempo_dispatch_out& d, cons
   gu.C = h;
   gu.Kd = s.H;
   gu.Nout = s.I;
-  gu.cmax = gateup_chunks(s);
+  gu.cmax = GATEUP_CHUNKS;
+  gu.whole = stream_whole_items(s) ? 1 : 0;
   auto mark = [&](int i) { return !ev || !ev[i] || hipEventRecord(ev[i], st) == hipSuccess; };
   if (!mark(0)) return hipErrorLaunchFailure;
   hipLaunchKernelGGL((k_gemm<false, BM, true>), dim3(grid), dim3(GEMM_THREADS), 0, st, gu);
   if (!mark(1)) return hipErrorLaunchFailure;
-  // (with one chunk per item no item is split: nothing to complete)
-  if (gu.cmax > 1)
+  // (without split items there is nothing to complete)
+  if (!gu.whole)
     hipLaunchKernelGGL((k_fixup<false, BM, true>), dim3(grid * (BM / 8)), dim3(256), 0, st, gu, grid);
   if (!mark(2)) return hipErrorLaunchFailure;
 
@@ -87,6 +90,23 @@ bool stream_gathers_rows(const tempo_moe_shape& s, const Layout& L) {
   const long long wfull = W_BASE + s.m_tile / 32, wmin = W_BASE + 1;
   const long long tiles = (max_tiles * wfull + wpx * wmin - 1) / (wpx * wmin) + 2;
   return tiles <= nrowt_of(s.m_tile);
+}
+
+// No partial tiles and no fixup launch, against a coarser balance of the
+// ranges.  Where the contraction is one chunk nothing is ever split; otherwise
+// whole items win unless they are few.  The slots that will be active are only
+// known on the device; the expected number, were the pairs spread evenly over
+// the experts, stands for them (the same for every plan and M-tile).
+// Measured, forward us split -> whole, weights from HBM (18 slots H 4096 I
+// 1536 unless said): bf16 16 tokens 76 -> 66, 32: 94 -> 91, 64: 113 -> 115,
+// 256: 170 -> 160, 512: 206 -> 199; fp8 16: 65 -> 58, 64: 83 -> 87, 128: 101 ->
+// 105, 256: 126 -> 117; 36 slots H 7168 I 2048 fp8 8: 100 -> 99, 64: 215 -> 209,
+// 256: 313 -> 310; H 256: 33 -> 30; but four slots of 96 items 55 -> 62, two
+// slots H 7168 I 2048 (64 items) 60 -> 73, six slots H 5120 I 1024 56 -> 67.
+bool stream_whole_items(const tempo_moe_shape& s) {
+  const int KT = s.H / (s.dtype == TEMPO_BF16 ? 64 : 128);
+  const double active = s.S * (1.0 - std::pow(1.0 - 1.0 / s.E, (double)s.T * s.K));
+  return KT <= 16 || active * (s.I / 64) >= 150.0;
 }
 
 hipError_t launch_experts_bf16(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,

@@ -103,13 +103,14 @@ hipError_t launch_bm(const tempo_moe_shape& s, const tempo_dispatch_out& d, cons
   gu.C = h32;
   gu.Kd = s.H;
   gu.Nout = s.I;
-  gu.cmax = gateup_chunks(s);
+  gu.cmax = GATEUP_CHUNKS;
+  gu.whole = stream_whole_items(s) ? 1 : 0;
   auto mark = [&](int i) { return !ev || !ev[i] || hipEventRecord(ev[i], st) == hipSuccess; };
   if (!mark(0)) return hipErrorLaunchFailure;
   hipLaunchKernelGGL((k_gemm<true, BM, true, MX>), dim3(grid), dim3(GEMM_THREADS), 0, st, gu);
   if (!mark(1)) return hipErrorLaunchFailure;
-  // (with one chunk per item no item is split: nothing to complete)
-  if (gu.cmax > 1)
+  // (without split items there is nothing to complete)
+  if (!gu.whole)
     hipLaunchKernelGGL((k_fixup<true, BM, true>), dim3(grid * (BM / 8)), dim3(256), 0, st, gu, grid);
   hipLaunchKernelGGL(k_quant_h<MX>, dim3(std::min(ceil_div(L.row_cap, 4), persistent_grid(8))), dim3(256), 0, st, h32, s.I, L.row_cap, d.row_token,
                      d.slot_offsets, s.S, h8, hs);

@@ -9,11 +9,12 @@
 // Work decomposition (stream-K over fixed contraction chunks).  A work item
 // is one (M-tile, output block of 128 weight rows) pair; its contraction of
 // KT steps (128 bytes of every row per step) is cut into C fixed chunks of
-// SPC steps (C at most GemmArgs::cmax), SPC a
+// SPC steps (C at most GemmArgs::cmax: 2 for gate/up, 1 for down), SPC a
 // multiple of CQ = 8 for every tile size (the last chunk is padded with
 // empty steps to a multiple of the pipeline depth DR).  The chunks of all items,
 // item by item, form one sequence that is split into contiguous ranges, one
-// per workgroup (one workgroup per CU).  Range boundaries balance estimated
+// per workgroup (one workgroup per CU), between any two chunks or, where that
+// is faster, between items only (GemmArgs::whole).  Boundaries balance estimated
 // time rather than chunk counts: a chunk of an M-tile with m live row blocks
 // of 32 weighs W_BASE + m (the fixed cost of a step plus its MFMA work), taken
 // from per-slot prefix sums in LDS.  When the output blocks divide by 8,
@@ -28,7 +29,8 @@
 // partial tile, and the workgroups holding the next chunks write each c_i to
 // a partial tile of their own.  A fixup kernel then adds the chunks in order
 // and applies the epilogue.  Results therefore do not depend on where the
-// range boundaries fall, on the plan, or on the tile a row lands in.
+// range boundaries fall, whether items are split at all, on the plan, on the
+// number of tokens or slots, or on the tile a row lands in.
 //
 // Memory pipeline.  A weight row block is used by exactly one wavefront
 // (wavefront w multiplies the item's rows 32w..32w+31), so weights skip LDS:
@@ -62,7 +64,6 @@
 // 16 bytes per lane.
 #pragma once
 
-#include <cmath>
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -106,27 +107,15 @@ struct GemmArgs {
   uint64_t* t1;
   int timing;
   int cmax;                 // contraction chunks per work item, 1 .. CMAX (1: items are never split)
+  int whole;                // 1: ranges end between items only (stream_whole_items): nothing for the fixup
 };
 
-// Chunks per item of the two GEMMs (GemmArgs::cmax).  Fewer chunks mean
-// fewer items split over workgroups, so fewer partial tiles to write and add
-// up, and with one no fixup pass, against a coarser balance of the ranges.
-// Down takes one: its output has many blocks, so whole items balance well.
-// gate/up takes one where its contraction is short or its items are about as
-// many as the workgroups, and two for a few long items.  The slots that will
-// be active are only known on the device; the expected number, were the pairs
-// spread evenly over the experts, stands for them (the same for every plan and
-// M-tile).  Measured, forward us with two -> one (18 slots H 4096 I 1536
-// unless said): bf16 16 tokens 82 -> 74, 32: 94 -> 88, 256: 176 -> 169, 512:
-// 211 -> 207; fp8 16: 70 -> 62, 64: 86 -> 88; 36 slots H 7168 I 2048 fp8 64:
-// 228 -> 220; H 256: 33 -> 30; but bf16 4 tokens (96 expected items) 57 -> 58,
-// four slots of 96 items 57 -> 64, two slots H 7168 I 2048 (64 items) 60 -> 72.
-inline int gateup_chunks(const tempo_moe_shape& s) {
-  const int KT = s.H / (s.dtype == TEMPO_BF16 ? 64 : 128);
-  const double active = s.S * (1.0 - std::pow(1.0 - 1.0 / s.E, (double)s.T * s.K));
-  return KT <= 16 || active * (s.I / 64) >= 150.0 ? 1 : 2;
-}
-constexpr int DOWN_CHUNKS = 1;
+// Chunks per item of the two GEMMs (GemmArgs::cmax): constants, so that a
+// row's products are summed in the same order in every batch.  More chunks
+// balance the ranges more finely, against more items split over workgroups
+// (partial tiles to write and add up).  gate/up is fastest with two, down with
+// one: its output has many blocks, so whole items balance well.
+constexpr int GATEUP_CHUNKS = 2, DOWN_CHUNKS = 1;
 
 // Steps in flight per wavefront (DR): the weight slices of DR steps sit in
 // registers (four 16-byte loads per lane and step), the activation rows of
@@ -156,7 +145,8 @@ struct Geo {
   int KT, SPC, C, SL;  // real steps per item; steps per chunk; chunks; steps of the last chunk (padded)
   int KTV;             // steps per item including the padding: (C - 1) * SPC + SL
   int groups, grp, j0, wpx, my_nb, nb_lo, items;
-  int q0, q1;          // this workgroup's chunk range [q0, q1)
+  int RC;              // chunks per unit of the ranges: 1, or C where they hold whole items
+  int q0, q1;          // this workgroup's chunk range [q0, q1), in whole units
 };
 
 __host__ __device__ __forceinline__ int geo_groups(int NB, int grid) { return (NB % 8 == 0 && grid % 8 == 0) ? 8 : 1; }
@@ -168,7 +158,7 @@ __host__ __device__ __forceinline__ int geo_groups(int NB, int grid) { return (N
 constexpr int W_BASE = 4;
 
 template <int BM>
-__device__ __forceinline__ int tile_weight(int rows) { return W_BASE + ((rows + 31) >> 5); }
+__host__ __device__ __forceinline__ int tile_weight(int rows) { return W_BASE + ((rows + 31) >> 5); }
 
 // By every wavefront for itself (all write the same s_sw); s_off / s_cnt must
 // be ready.  Lane l sums slots 4l .. 4l + 3, then a shuffle scan; end[i]:
@@ -206,18 +196,18 @@ __device__ __forceinline__ void build_slot_weights(const int32_t* s_off, const i
   wait_lgkm0();
 }
 
-// First chunk of workgroup j of a group: the smallest chunk q whose weight
-// prefix reaches j / wpx of the total.  INT: the type of the arithmetic (32
-// bits where unit * s_sw[S] * wpx fits).  first(unit, T): the first slot whose
-// end, unit * s_sw[s + 1], lies beyond T.
+// First chunk of workgroup j of a group: that of the smallest range unit (a
+// chunk, or an item) whose weight prefix reaches j / wpx of the total.  INT:
+// the type of the arithmetic (32 bits where unit * s_sw[S] * wpx fits).
+// first(unit, T): the first slot whose end, unit * s_sw[s + 1], lies beyond T.
 template <int BM, typename INT, typename F>
-__device__ __forceinline__ int range_from(const Geo& g, int j, const int32_t* s_off, const int32_t* s_cnt,
+__host__ __device__ __forceinline__ int range_from(const Geo& g, int j, const int32_t* s_off, const int32_t* s_cnt,
                                           const int32_t* s_sw, int S, F first) {
   const int U = g.items * g.C;
   if (j <= 0) return 0;
   if (j >= g.wpx) return U;
-  const INT unit = (INT)g.my_nb * g.C;       // chunks per M-tile
-  const INT T = unit * s_sw[S] * j / g.wpx;  // target weight
+  const INT unit = (INT)g.my_nb * (g.C / g.RC);  // range units per M-tile
+  const INT T = unit * s_sw[S] * j / g.wpx;      // target weight
   const int lo = first(unit, T);
   if (lo == S) return U;
   const int nt = (s_off[lo + 1] - s_off[lo]) / BM;  // >= 1
@@ -226,7 +216,7 @@ __device__ __forceinline__ int range_from(const Geo& g, int j, const int32_t* s_
   const INT tf = min(rem / wf, (INT)(nt - 1));  // whole tiles of the slot before the target
   const int wt = tf < nt - 1 ? tile_weight<BM>(BM) : tile_weight<BM>(s_cnt[lo] - (nt - 1) * BM);
   const INT r = min((INT)((rem - tf * wf + wt - 1) / wt), unit);
-  const long long q = (long long)(s_off[lo] / BM + tf) * unit + r;
+  const long long q = ((long long)(s_off[lo] / BM + tf) * unit + r) * g.RC;
   return (int)min(q, (long long)U);
 }
 
@@ -246,13 +236,14 @@ __device__ int range_lo(const Geo& g, int j, const int32_t* s_off, const int32_t
 template <int BM>
 __device__ __forceinline__ Geo make_geo(int KT, int NB, int NT, int b, int grid, const int32_t* s_off,
                                         const int32_t* s_cnt, const int32_t* s_sw, int S, int cmax,
-                                        const int (&end)[4]) {
+                                        int whole, const int (&end)[4]) {
   Geo g;
   constexpr int DR = gemm_dr(BM);
   g.KT = KT;
   const int cm = min(max(cmax, 1), CMAX);
   g.SPC = ((KT + cm - 1) / cm + CQ - 1) / CQ * CQ;
   g.C = (KT + g.SPC - 1) / g.SPC;
+  g.RC = whole ? g.C : 1;
   g.SL = (KT - (g.C - 1) * g.SPC + DR - 1) / DR * DR;
   g.KTV = (g.C - 1) * g.SPC + g.SL;
   g.groups = geo_groups(NB, grid);
@@ -272,7 +263,7 @@ __device__ __forceinline__ Geo make_geo(int KT, int NB, int NT, int b, int grid,
     for (int i = 0; i < 4; i++) n += __popcll(__ballot(4 * l + i < S && unit * end[i] <= T));
     return n;
   };
-  if ((long long)g.my_nb * g.C * s_sw[S] * g.wpx < (1ll << 31)) {
+  if ((long long)g.my_nb * (g.C / g.RC) * s_sw[S] * g.wpx < (1ll << 31)) {
     g.q0 = range_from<BM, int>(g, g.j0, s_off, s_cnt, s_sw, S, first);
     g.q1 = range_from<BM, int>(g, g.j0 + 1, s_off, s_cnt, s_sw, S, first);
   } else {
@@ -358,7 +349,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void k_gemm(const GemmArgs p) {
   // multiple of BM), bounded by what the row buffers hold
   const int NT = __builtin_amdgcn_readfirstlane(max(0, min(s_off[p.S] / BM, p.max_tiles)));
   const Geo g = make_geo<BM>(p.Kd / BK, p.Nout / NCOLS, NT, blockIdx.x, gridDim.x, s_off, s_cnt, s_sw, p.S, p.cmax,
-                             sw_end);
+                             p.whole, sw_end);
   if (g.q0 >= g.q1) {  // uniform: the whole workgroup leaves
     if (tid == 0) p.fix[(size_t)blockIdx.x * FIX_WORDS] = -1;
     return;

@@ -129,14 +129,18 @@ hipError_t launch_pack(const tempo_moe_shape& s, const tempo_expert_weights& nat
 // written (by stage 1, or by the pack step of the wide-tile kernels).
 bool experts_gather_rows(const tempo_moe_shape& s, const Layout& L);
 bool stream_gathers_rows(const tempo_moe_shape& s, const Layout& L);
+// Whether the streaming gate/up GEMM deals whole items to its workgroups
+// (otherwise their ranges may end inside an item, which a fixup completes).
+bool stream_whole_items(const tempo_moe_shape& s);
 bool experts_reads_token_scales(const tempo_moe_shape& s, const Layout& L);
 
 // Kernel family that stage 2 of a shape runs on (tempo_internal_stage2_route).
 enum Stage2Route : int {
-  kRouteStream = 0,  // k_gemm (stream-K)
-  kRouteBig = 1,     // k_gemm_big
-  kRouteBigF8 = 2,   // k_gemm_big_f8
-  kRouteWide = 3,    // k_gemm_wide
+  kRouteStream = 0,       // k_gemm (stream-K), gate/up ranges of whole items
+  kRouteStreamSplit = 1,  // k_gemm, gate/up ranges of contraction chunks, and k_fixup
+  kRouteBig = 2,          // k_gemm_big
+  kRouteBigF8 = 3,        // k_gemm_big_f8
+  kRouteWide = 4,         // k_gemm_wide
 };
 
 // Whether stage-2 kernels exist for this shape's element type and M-tile.

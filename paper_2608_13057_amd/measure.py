@@ -67,13 +67,14 @@ def auto_m_tile(wl) -> int:
     return 256
 
 
-ROUTES = ("stream", "big", "big_f8", "wide")
+ROUTES = ("stream", "stream_split", "big", "big_f8", "wide")
 
 
 def stage2_route(shape) -> str:
     """The kernel family stage 2 of a moe.MoEShape runs on, as the library
-    chooses it from the shape: "stream" (stream-K), "big" / "big_f8" (256-row
-    large tiles, bf16 / UE8M0 fp8) or "wide" (wide tiles)."""
+    chooses it from the shape: "stream" (stream-K, whole items per workgroup),
+    "stream_split" (stream-K, gate/up items split over workgroups), "big" /
+    "big_f8" (256-row large tiles, bf16 / UE8M0 fp8) or "wide" (wide tiles)."""
     import ctypes
 
     from . import _lib
@@ -91,7 +92,7 @@ def gateup_kernel_name(shape) -> str:
     route = stage2_route(shape)
     if route == "wide":
         return f"tempo::(anonymous namespace)::k_gemm_wide<{('fp8', 'fp8mx', 'bf16').index(shape.dtype)}, true>"
-    if route != "stream":
+    if not route.startswith("stream"):
         return f"tempo::(anonymous namespace)::k_gemm_{route}<true>"
     fp8 = "false" if shape.dtype == "bf16" else "true"
     mx = "true" if shape.dtype == "fp8mx" else "false"

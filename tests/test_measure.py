@@ -45,6 +45,7 @@ def test_kernel_classification():
 
 @pytest.mark.parametrize("dtype,T,S,H,I,m_tile,route,name", [
     ("bf16", 512, 18, 4096, 1536, 64, "stream", "k_gemm<false, 64, true, false>"),
+    ("bf16", 4, 18, 4096, 1536, 64, "stream_split", "k_gemm<false, 64, true, false>"),
     ("fp8", 64, 18, 4096, 1536, 256, "stream", "k_gemm<true, 256, true, false>"),
     ("fp8mx", 64, 18, 4096, 1408, 256, "stream", "k_gemm<true, 256, true, true>"),
     ("bf16", 64, 18, 4096, 1536, 256, "big", "k_gemm_big<true>"),
