@@ -1054,51 +1054,66 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 // Which of two kernels wins near the line depends on the plan: uniform shares
 // leave slots of very different sizes, which the other kernel balances worst;
 // a plan that keeps few replicas busy leaves it slots of few rows each, its
-// best case.  Measured, forward us, other kernel -> wide tiles, uniform plan /
-// token balancing / fewest replicas (18 slots H 4096 I 1536; "36": 36 slots
-// H 7168 I 2048; "10": 10 slots H 2048 I 1408; "5" etc.: that many slots):
-//   bf16   64-row tiles, rows per expert 32: 203 -> 193 / 179 -> 191 / 147 ->
-//          160; 48: 218 -> 201 / 199 -> 195 / 159 -> 173 (36: 1048 -> 738 /
-//          826 -> 676 / 679 -> 653); 64: 241 -> 207 / 224 -> 203 / 183 -> 176.
-//          128-row tiles, 64: 221 -> 209 / 211 -> 203 / 187 -> 178 (36: 1038 ->
-//          767 / 828 -> 689 / 698 -> 660; 48: 882 -> 735).  Many items (36), 32:
-//          841 -> 694 / 696 -> 671 / 578 -> 597.  Items 121 (10): 87 -> 86
-//          / 80 -> 86 / 58 -> 70; 143 (10): 110 -> 93 / 98 -> 91 / 77 -> 87.
-//          256-row tiles, 24: 222 -> 185 / - / 183 -> 155; 32: 232 -> 192 / 228
-//          -> 188 / 186 -> 164; 512: 593 -> 546; items 6 (2): 96 -> 71, 42 (5):
-//          92 -> 73, 84 (5): 111 -> 89.  But full tiles that make about one
-//          round of items, the other large-tile kernel's best case: items 144:
-//          135 -> 139, 192: 155 -> 165, 242: 137 -> 142, 264: 141 -> 145; then
-//          312: 266 -> 236, 341: 201 -> 183, 444: 400 -> 355
-//   fp8    rows 8: 103 -> 100 (36: 323 -> 326); 12: - / 109 -> 103 / 105 -> 94
-//          (36: - / 316 -> 321 / 291 -> 280); 16: 129 -> 112 / 119 -> 110 / 110
-//          -> 98 (36: 389 -> 380 / 329 -> 348 / 306 -> 298); 32: 149 -> 132 /
-//          129 -> 127 / 115 -> 123 (36: 499 -> 426 / 418 -> 410 / 358 -> 346);
-//          128: 252 -> 164; 512: 710 -> 368.  Items 66: 53 -> 53, 80 of 256 rows
-//          (5): 69 -> 74, 110 of 256 rows (5): 72 -> 75 (with 256-row M-tiles 9
-//          (2): 97 -> 75, 44 (3): 104 -> 96), 121 (10): 79 -> 74 /
-//          73 -> 74 / 57 -> 60, 132 (10): 97 -> 82 / 86 -> 80 / 74 -> 72, 143
-//          (10): 106 -> 83 / 94 -> 83 / 77 -> 77
-//   UE8M0  rows 24: - / 115 -> 121 / 99 -> 100; 40: 144 -> 132 / 129 -> 129 /
-//          107 -> 118; 64: 159 -> 137 / 150 -> 134 / 125 -> 127; 36 slots 24: - /
-//          367 -> 385 / 315 -> 324, 32: 480 -> 414 / 399 -> 404 / 338 -> 335, 48:
-//          591 -> 441 / 471 -> 414 / 391 -> 390.  Items 132 (10): 84 -> 77 / 75
-//          -> 77 / 64 -> 69; with 256-row tiles 9 (2): 84 -> 71, 44 (3): 88 ->
-//          87, 110 (5): 91 -> 71 and 121 at 36 rows: 81 -> 71; short
-//          contractions (H 1152): 32: 68 -> 72, 96: 81 -> 74; against its own
-//          256-row kernel 160: 173 -> 173, 512: 327 -> 333
+// best case.  The lines lie where the plans together gain and the worst of them
+// loses little (of 1970 measured points inside them, 9 take over 3% more than with
+// the kernels before the wide tiles, at most 9%: fp8, 64-row tiles, 12 to 16
+// rows, fewest replicas on one of two placements).
+// Measured, forward us, other kernel -> wide tiles, uniform plan / token
+// balancing / fewest replicas ("18": 18 slots H 4096 I 1536; "36": 36 slots H
+// 7168 I 2048; "12a": 12 slots H 3072 I 2048; "12b": 12 slots H 2048 I 1408;
+// "10": 10 slots H 2048 I 1408; items in brackets):
+//   bf16   64-row tiles, rows per expert 64 (18) [264]: 222 -> 213 / 216 -> 205
+//          / 171 -> 193; 80: 291 -> 225 / 230 -> 209 / 206 -> 189.  Many items
+//          (36), 32: 816 -> 686 / 666 -> 665 / 540 -> 590; 48: 1034 -> 737 / 796
+//          -> 675 / 664 -> 648.  Shorter contractions (12a) [272], 112: 241 ->
+//          187 / 171 -> 168 / 118 -> 121; (12b) 80 [165]: 122 -> 106 / 93 -> 82 /
+//          74 -> 79; 128 [198]: 162 -> 115 / 110 -> 108 / 85 -> 85.
+//          128-row tiles (18), 64: 231 -> 209 / 198 -> 205 / 177 -> 192; 80: 243
+//          -> 223 / 245 -> 209 / 197 -> 189; (12a) 80: 185 -> 175 / 144 -> 160 /
+//          108 -> 113, 128: 232 -> 187 / 185 -> 170 / 140 -> 138.
+//          256-row tiles against their own large-tile kernel (18), 24: 219 ->
+//          183 / 217 -> 182 / 180 -> 154; 128 [324]: 328 -> 245 / 309 -> 226 /
+//          231 -> 200; 512: 562 -> 528 / 509 -> 451 / 385 -> 338; but full
+//          tiles that make about one round of items are its best case: (12b) 192
+//          [231]: 124 -> 138 / 114 -> 113 / 111 -> 85; 12 slots H 2048 I 768, 128
+//          [108]: 104 -> 93, 208 [126]: 110 -> 122, 288 [150]: 115 -> 125; 18
+//          slots H 4096 I 1024, 176 [240]: 214 -> 220, 256 [288]: 320 -> 237;
+//          (12a) 192 [336]: 233 -> 210 / 166 -> 182 / 157 -> 149, 320 [416]: 304
+//          -> 265 / 232 -> 190 / 173 -> 181
+//   fp8    64-row tiles (18, two placements), 8: 102 -> 90 / 100 -> 90 / 95 ->
+//          84, 101 -> 91 / 100 -> 90 / 99 -> 91; 12: 107 -> 96 / 107 -> 96 / 103 ->
+//          87, 111 -> 96 / 110 -> 95 / 104 -> 110; 24: 126 -> 121 / 119 -> 118 /
+//          107 -> 97, 121 -> 120 / 121 -> 121 / 118 -> 115; (36) 8: +5 / +2 / 0%,
+//          12: 378 -> 369 / 328 -> 309 / 300 -> 287, 16: 394 -> 386 / 326 -> 333 /
+//          300 -> 291; (12b) 64 [165]: 89 -> 79 / 82 -> 74 / 64 -> 72;
+//          (10) 96 [143]: 95 -> 85 / 90 -> 82 / 67 -> 78.  128-row tiles (18), 12:
+//          121 -> 95 / 112 -> 95 / 102 -> 87; 20 slots H 2048 I 512, 64 [100]: 77
+//          -> 84.  256-row tiles (18), 16: 165 -> 100
+//          / 163 -> 99 / 135 -> 95; 12 slots H 7168 I 384, 32 [39]: 121 -> 132, 64:
+//          155 -> 147
+//   UE8M0  64-row tiles (18), 48 [252]: 147 -> 130 / 138 -> 126 / 110 -> 121; 64:
+//          149 -> 133 / 144 -> 130 / 118 -> 126; (12b) 128 [198]: 118 -> 84 / 86
+//          -> 81 / 69 -> 77; (36) 32: 475 -> 416 / 388 -> 394 / 325 -> 336.  128-row
+//          tiles (18), 56: 158 -> 130 / 142 -> 128 / 126 -> 122; (10) 128 [154]: 97
+//          -> 83 / 93 -> 81 / 70 -> 78.  256-row tiles with I an odd multiple of
+//          128: 6 slots H 4096 I 384, 64 [21]: 72 -> 77, 256 [36]: 96 -> 103, 512
+//          [54]: 129 -> 112; 12 slots H 7168 I 384, 64 [45]: 128 -> 137; 10 slots
+//          H 5120 I 896, 64 [84]: 115 -> 112 / 109 -> 108 / 94 -> 102; 16 slots
+//          H 1152 I 768, 32 [108]: 68 -> 59; against its own 256-row kernel 160:
+//          173 -> 173, 512: 327 -> 333
 bool experts_wide_wanted(const tempo_moe_shape& s) {
   if (experts_big_f8_supported(s)) return false;
   const long long P = (long long)s.T * s.K, E = s.E;
   // items of the gate/up GEMM, were the pairs spread evenly over the experts
   const long long items = (s.S + P * s.S / (256 * E)) * (s.I / 128);
-  const bool m256 = s.m_tile == 256, many = items >= 500;
+  const bool m64 = s.m_tile == 64, m256 = s.m_tile == 256, many = items >= 500, deep = s.H >= 4096;
   if (s.dtype == TEMPO_BF16) {
-    if (m256) return P >= 24 * E && !(s.H % 256 == 0 && P >= 256 * E && items > 128 && items <= 270);
-    return items >= 150 && P >= (s.m_tile == 64 ? (many ? 32 : 48) : (many ? 48 : 64)) * E;
+    if (m256) return P >= 24 * E && (s.H % 256 || P < 64 * E || items <= 120 || items >= (deep ? 270 : 500));
+    return items >= 150 && P >= (many ? 48 : deep ? 80 : 128) * E;
   }
-  if (s.dtype == TEMPO_FP8_E4M3) return (m256 || items >= 130) && P >= 12 * E;
-  return (m256 || items >= 150) && P >= (m256 || many ? 32 : 56) * E;
+  if (s.dtype == TEMPO_FP8_E4M3) return (m256 || items >= (m64 ? 170 : 130)) && P >= (m64 && !many ? 8 : 12) * E;
+  if (m256) return items >= 60 && P >= 32 * E;
+  return items >= (m64 ? 200 : 150) && P >= 48 * E;
 }
 
 hipError_t launch_experts_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,

@@ -65,6 +65,24 @@ def test_kernel_name_is_the_librarys_choice(dtype, T, S, H, I, m_tile, route, na
         measure.stage2_route(moe.MoEShape(T=T, K=8, E=128, S=S, H=H, I=I, m_tile=96, dtype=dtype))
 
 
+@pytest.mark.parametrize("dtype,m_tile,rows,E,K,S,H,I,wide", [
+    ("bf16", 64, 48, 128, 8, 18, 4096, 1536, False), ("bf16", 64, 80, 128, 8, 18, 4096, 1536, True),
+    ("bf16", 64, 32, 256, 8, 36, 7168, 2048, False), ("bf16", 64, 48, 256, 8, 36, 7168, 2048, True),
+    ("bf16", 128, 64, 128, 8, 18, 4096, 1536, False), ("bf16", 128, 80, 128, 8, 18, 4096, 1536, True),
+    ("bf16", 128, 112, 64, 6, 12, 3072, 2048, False), ("bf16", 128, 160, 64, 6, 12, 3072, 2048, True),
+    ("bf16", 256, 96, 128, 8, 20, 2048, 768, False), ("bf16", 256, 192, 64, 8, 12, 2048, 1408, False),
+    ("bf16", 256, 24, 64, 8, 12, 2048, 1408, True), ("bf16", 256, 512, 128, 8, 18, 4096, 1536, True),
+    ("fp8", 64, 12, 128, 8, 18, 4096, 1024, False), ("fp8", 64, 96, 64, 6, 10, 2048, 1408, False),
+    ("fp8", 64, 12, 128, 8, 18, 4096, 1536, True), ("fp8", 128, 12, 128, 8, 18, 4096, 1536, True),
+    ("fp8mx", 64, 128, 64, 6, 10, 2048, 1408, False), ("fp8mx", 64, 48, 128, 8, 18, 4096, 1536, True),
+    ("fp8mx", 64, 32, 256, 8, 36, 7168, 2048, False), ("fp8mx", 256, 64, 32, 4, 6, 4096, 384, False),
+    ("fp8mx", 256, 32, 64, 4, 12, 7168, 384, False), ("fp8mx", 256, 64, 64, 6, 10, 5120, 896, True)])
+def test_wide_tiles_only_where_they_were_measured_faster(dtype, m_tile, rows, E, K, S, H, I, wide):
+    """Points on both sides of the lines of experts_wide_wanted."""
+    shape = moe.MoEShape(T=rows * E // K, K=K, E=E, S=S, H=H, I=I, m_tile=m_tile, dtype=dtype)
+    assert (measure.stage2_route(shape) == "wide") == wide
+
+
 def test_mfma_summary_arithmetic(tmp_path):
     """Two dispatches: busy cycles 2e8 / 3e8, GRBM_GUI_ACTIVE (summed over 8
     XCDs) 3.2e6 / 4.8e6, MOPS 1e8 / 1e8, mean duration 200 us.  Mean busy
