@@ -95,8 +95,8 @@ bool stream_gathers_rows(const tempo_moe_shape& s, const Layout& L) {
 // No partial tiles and no fixup launch, against a coarser balance of the
 // ranges.  Where the contraction is one chunk nothing is ever split; otherwise
 // whole items win unless they are few.  The slots that will be active are only
-// known on the device; the expected number, were the pairs spread evenly over
-// the experts, stands for them (the same for every plan and M-tile).
+// known on the device; the expected number, were the valid pairs spread evenly
+// over the experts, stands for them (the same for every plan and M-tile).
 // Measured, forward us split -> whole, weights from HBM (18 slots H 4096 I
 // 1536 unless said): bf16 16 tokens 76 -> 66, 32: 94 -> 91, 64: 113 -> 115,
 // 256: 170 -> 160, 512: 206 -> 199; fp8 16: 65 -> 58, 64: 83 -> 87, 128: 101 ->
@@ -105,7 +105,7 @@ bool stream_gathers_rows(const tempo_moe_shape& s, const Layout& L) {
 // slots H 7168 I 2048 (64 items) 60 -> 73, six slots H 5120 I 1024 56 -> 67.
 bool stream_whole_items(const tempo_moe_shape& s) {
   const int KT = s.H / (s.dtype == TEMPO_BF16 ? 64 : 128);
-  const double active = s.S * (1.0 - std::pow(1.0 - 1.0 / s.E, (double)s.T * s.K));
+  const double active = s.S * (1.0 - std::pow(1.0 - 1.0 / s.E, (double)s.T_valid * s.K));
   return KT <= 16 || active * (s.I / 64) >= 150.0;
 }
 

@@ -1048,9 +1048,12 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 }  // namespace
 
 // Where the wide tiles win: slots with enough rows, and enough items to fill
-// the chip.  The counts per slot are only known on the device; rows per
-// expert, T K / E, and the items that these make, stand for them (the same
-// for every plan, so a row's result does not depend on it).
+// the chip.  The counts per slot are only known on the device; valid rows per
+// expert, T_valid K / E, and the items that these make, stand for them (the same
+// for every plan, so a row's result does not depend on it; padding tokens make
+// no rows: of 1024 tokens half of them valid, judged by all -> by the valid ones,
+// 18 slots 195 -> 199 / 196 -> 176 / 176 -> 152 us, 36 slots 657 -> 642 / 585 ->
+// 532 / 528 -> 481).
 // Which of two kernels wins near the line depends on the plan: uniform shares
 // leave slots of very different sizes, which the other kernel balances worst;
 // a plan that keeps few replicas busy leaves it slots of few rows each, its
@@ -1103,7 +1106,7 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 //          173 -> 173, 512: 327 -> 333
 bool experts_wide_wanted(const tempo_moe_shape& s) {
   if (experts_big_f8_supported(s)) return false;
-  const long long P = (long long)s.T * s.K, E = s.E;
+  const long long P = (long long)s.T_valid * s.K, E = s.E;
   // items of the gate/up GEMM, were the pairs spread evenly over the experts
   const long long items = (s.S + P * s.S / (256 * E)) * (s.I / 128);
   const bool m64 = s.m_tile == 64, m256 = s.m_tile == 256, many = items >= 500, deep = s.H >= 4096;

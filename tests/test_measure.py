@@ -83,6 +83,19 @@ def test_wide_tiles_only_where_they_were_measured_faster(dtype, m_tile, rows, E,
     assert (measure.stage2_route(shape) == "wide") == wide
 
 
+def test_padding_tokens_do_not_choose_the_kernel():
+    """A padded batch runs on the kernels of the batch it holds: padding
+    tokens make no rows.  (Sizes on both sides of every line of the rules.)"""
+    for dtype in ("bf16", "fp8", "fp8mx"):
+        for m_tile in (64, 128, 192, 256):
+            for E, K, S, H, I in ((128, 8, 18, 4096, 1536), (256, 8, 36, 7168, 2048), (64, 6, 10, 2048, 1408), (16, 2, 2, 7168, 384)):
+                kw = dict(K=K, E=E, S=S, H=H, I=I, m_tile=m_tile, dtype=dtype)
+                for Tv in (1, 4, 40, 130, 200, 400, 700, 1100, 1700, 3000, 6000, 9000):
+                    route = measure.stage2_route(moe.MoEShape(T=Tv, **kw))
+                    for T in (Tv + 1, 2 * Tv, 16 * Tv):
+                        assert measure.stage2_route(moe.MoEShape(T=T, T_valid=Tv, **kw)) == route, (kw, Tv, T)
+
+
 def test_mfma_summary_arithmetic(tmp_path):
     """Two dispatches: busy cycles 2e8 / 3e8, GRBM_GUI_ACTIVE (summed over 8
     XCDs) 3.2e6 / 4.8e6, MOPS 1e8 / 1e8, mean duration 200 us.  Mean busy
