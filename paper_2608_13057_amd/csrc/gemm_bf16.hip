@@ -93,20 +93,28 @@ bool stream_gathers_rows(const tempo_moe_shape& s, const Layout& L) {
 }
 
 // No partial tiles and no fixup launch, against a coarser balance of the
-// ranges.  Where the contraction is one chunk nothing is ever split; otherwise
-// whole items win unless they are few.  The slots that will be active are only
-// known on the device; the expected number, were the valid pairs spread evenly
-// over the experts, stands for them (the same for every plan and M-tile).
-// Measured, forward us split -> whole, weights from HBM (18 slots H 4096 I
-// 1536 unless said): bf16 16 tokens 76 -> 66, 32: 94 -> 91, 64: 113 -> 115,
-// 256: 170 -> 160, 512: 206 -> 199; fp8 16: 65 -> 58, 64: 83 -> 87, 128: 101 ->
-// 105, 256: 126 -> 117; 36 slots H 7168 I 2048 fp8 8: 100 -> 99, 64: 215 -> 209,
-// 256: 313 -> 310; H 256: 33 -> 30; but four slots of 96 items 55 -> 62, two
-// slots H 7168 I 2048 (64 items) 60 -> 73, six slots H 5120 I 1024 56 -> 67.
+// ranges: what whole items lose grows with the time of an item, what they save
+// does not.  64-row tiles wait for their weights, an item's time goes with its
+// steps; larger ones for the MFMAs too, its time goes with H.  64-row tiles
+// with long contractions gain where the items are about as many as the workgroups
+// or more, and lose where a fraction of the workgroups holds them all.  The
+// slots that will be active are only known on the device; the expected number,
+// were the valid pairs spread evenly over the experts, stands for them (the
+// same for every plan).  Measured, forward us split -> whole, by expected
+// items over 256 workgroups (x):
+//   64-row tiles   bf16 H 4096 I 1536 18 slots 16 tokens (x 1.07) 77 -> 68, 32
+//          (1.46) 89 -> 83, 64 (1.66) 106 -> 110, 256 (1.69) 155 -> 152, 512 203 ->
+//          198; H 5120 I 2048 5 slots (0.62) 8 rows per expert 68 -> 74; H 7168 I
+//          2048 2 slots (0.25) 64 -> 75, 36 slots (2.9 .. 4.5) -2.5 .. +2.5%; H
+//          1152 (18 steps) 48 -> 43; fp8 H 3072 (24 steps) (0.4 .. 0.6) -6 .. +2 us
+//   128-row tiles  bf16 H 1152 68 -> 60, fp8 63 -> 55; H 2048 bf16 -10 .. +6 us, H
+//          3072 -9 .. +14, H 4096 18 slots -12 .. +11, 6 slots +6 .. +17
+//   256-row tiles  H 1152 -6 .. 0 us, H 4096 fp8 18 slots 0 .. +14
 bool stream_whole_items(const tempo_moe_shape& s) {
+  if (s.m_tile > 64) return s.H <= 1280;
   const int KT = s.H / (s.dtype == TEMPO_BF16 ? 64 : 128);
   const double active = s.S * (1.0 - std::pow(1.0 - 1.0 / s.E, (double)s.T_valid * s.K));
-  return KT <= 16 || active * (s.I / 64) >= 150.0;
+  return KT <= 24 || active * (s.I / 64) >= 0.7 * 256;
 }
 
 hipError_t launch_experts_bf16(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,

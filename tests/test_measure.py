@@ -46,8 +46,8 @@ def test_kernel_classification():
 @pytest.mark.parametrize("dtype,T,S,H,I,m_tile,route,name", [
     ("bf16", 512, 18, 4096, 1536, 64, "stream", "k_gemm<false, 64, true, false>"),
     ("bf16", 4, 18, 4096, 1536, 64, "stream_split", "k_gemm<false, 64, true, false>"),
-    ("fp8", 64, 18, 4096, 1536, 256, "stream", "k_gemm<true, 256, true, false>"),
-    ("fp8mx", 64, 18, 4096, 1408, 256, "stream", "k_gemm<true, 256, true, true>"),
+    ("fp8", 64, 18, 4096, 1536, 256, "stream_split", "k_gemm<true, 256, true, false>"),
+    ("fp8mx", 64, 18, 1152, 1408, 256, "stream", "k_gemm<true, 256, true, true>"),
     ("bf16", 64, 18, 4096, 1536, 256, "big", "k_gemm_big<true>"),
     ("fp8mx", 8192, 18, 4096, 1536, 256, "big_f8", "k_gemm_big_f8<true>"),
     ("bf16", 8192, 18, 4096, 1536, 256, "wide", "k_gemm_wide<2, true>"),
@@ -81,6 +81,20 @@ def test_wide_tiles_only_where_they_were_measured_faster(dtype, m_tile, rows, E,
     """Points on both sides of the lines of experts_wide_wanted."""
     shape = moe.MoEShape(T=rows * E // K, K=K, E=E, S=S, H=H, I=I, m_tile=m_tile, dtype=dtype)
     assert (measure.stage2_route(shape) == "wide") == wide
+
+
+@pytest.mark.parametrize("dtype,m_tile,rows,E,K,S,H,I,whole", [
+    ("bf16", 64, 2, 128, 8, 18, 4096, 1536, True), ("bf16", 64, 16, 32, 4, 5, 5120, 2048, False),
+    ("bf16", 64, 8, 16, 2, 2, 7168, 2048, False), ("bf16", 64, 8, 256, 8, 36, 7168, 2048, True),
+    ("bf16", 64, 8, 96, 8, 12, 1536, 768, True), ("bf16", 128, 24, 128, 8, 18, 4096, 1536, False),
+    ("bf16", 128, 128, 64, 4, 10, 3072, 1024, False), ("bf16", 128, 24, 96, 6, 16, 1152, 768, True),
+    ("fp8", 64, 4, 64, 4, 10, 3072, 1024, True), ("fp8", 64, 4, 32, 4, 5, 5120, 2048, False),
+    ("fp8", 128, 24, 128, 8, 20, 2048, 512, False), ("fp8", 256, 8, 128, 8, 18, 4096, 1536, False),
+    ("fp8mx", 256, 16, 96, 6, 16, 1152, 640, True), ("fp8mx", 128, 64, 32, 4, 5, 5120, 2048, False)])
+def test_items_stay_whole_only_where_that_was_measured_faster(dtype, m_tile, rows, E, K, S, H, I, whole):
+    """Points on both sides of the lines of stream_whole_items."""
+    shape = moe.MoEShape(T=rows * E // K, K=K, E=E, S=S, H=H, I=I, m_tile=m_tile, dtype=dtype)
+    assert measure.stage2_route(shape) == ("stream" if whole else "stream_split")
 
 
 def test_padding_tokens_do_not_choose_the_kernel():
