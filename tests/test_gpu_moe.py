@@ -187,11 +187,10 @@ def test_forward_256_row_tiles_every_live_block_count(dtype):
 
 @pytest.mark.parametrize("dtype,I", [("fp8mx", 512), ("bf16", 128)])
 def test_forward_256_row_tiles_shallow_items(dtype, I):
-    """The large-tile kernels with the fewest sub-steps per item and several
-    items per workgroup: H 256 (a UE8M0 gate/up item is then four sub-steps,
+    """The UE8M0 large-tile kernel with the fewest sub-steps per item and several
+    items per workgroup: H 256 (a gate/up item is then four sub-steps,
     as many as its operand ring holds; both GEMMs run the same item cursor)
-    and, for bf16, I 128 (a down item of eight sub-steps, one less than its
-    ring), 64 experts of 1000..1199 rows in over 300 M-tiles, so the DMA
+    and, for bf16 on wide tiles, I 128 (two steps per down item), 64 experts of 1000..1199 rows in over 300 M-tiles, so the DMA
     cursor of every workgroup is an item or more ahead when an item starts.
     y on a token sample with one row of every M-tile and every slot's last
     row against the fp64 oracle (exact and mirror modes); tokens with no
@@ -234,7 +233,8 @@ def test_forward_256_row_tiles_shallow_items(dtype, I):
 @pytest.mark.parametrize("seed", [0, 1, 2])
 @pytest.mark.parametrize("dtype", ["fp8mx", "bf16"])
 def test_forward_256_row_tiles_random_shapes(dtype, seed):
-    """The large-tile kernels on random shapes each accepts: H from 256 to
+    """256-row M-tiles, by the large-tile kernels or (bf16 sizes of another
+    number of items) the wide tiles, on random shapes: H from 256 to
     1280, I from the smallest multiple each takes (UE8M0: 256, bf16: 128)
     up to 1024, 3..24 experts of 1..900 rows routed top-1 or top-2 over
     uniform or hot placements; stage 1 bit-exact, y on a token sample with
@@ -338,9 +338,9 @@ def test_forward_wide_tiles(dtype, m_tile, H, reps):
 @pytest.mark.parametrize("m_tile", [64, 128, 192, 256])
 @pytest.mark.parametrize("dtype", ["bf16", "fp8", "fp8mx"])
 def test_forward_stream_k_random_shapes(dtype, m_tile):
-    """The stream-K kernel on random shapes: H and I multiples of 128 (at
-    M 256, H an odd multiple of 128, where the large-tile kernels do not
-    apply and stream-K takes the tile), 3..24 experts of 1..700 rows routed
+    """Random shapes that none of the 256-row large-tile kernels takes: H and I
+    multiples of 128 (at M 256, H an odd multiple of 128), by the stream-K
+    kernel or, where the rows are many, the wide tiles; 3..24 experts of 1..700 rows routed
     top-1..top-4, some with a second slot, a few padding tokens; stage 1
     bit-exact, y on a token sample (one row of every M-tile, every slot's
     last row and 400 random tokens) against the fp64 oracle in exact and

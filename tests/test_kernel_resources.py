@@ -1,11 +1,11 @@
-"""Register and LDS budget of the large-tile stage-2 GEMMs (bf16 and UE8M0
-fp8), from the compiler's kernel metadata (CPU only: hipcc cross-compiles for
-gfx950).
+"""Register and LDS budget of the large-tile (bf16 and UE8M0 fp8) and
+wide-tile stage-2 GEMMs, from the compiler's kernel metadata (CPU only: hipcc
+cross-compiles for gfx950).
 
-The kernel streams its operands with LDS DMA issued from inline assembly,
+The kernels stream their operands with LDS DMA issued from inline assembly,
 which the compiler does not track; a register spill makes it wait for every
 vector-memory load in flight before the reload, which drains the DMA ring.
-So the kernel must compile without spills, and its ring must fit the 160 KB
+So they must compile without spills, and their rings must fit the 160 KB
 of LDS of a gfx950 CU.
 """
 import os
@@ -50,5 +50,18 @@ def test_large_tile_gemm_has_no_spills_and_fits_lds(tmp_path, which):
         # in scalar registers; the spilled values are read per item, not
         # per sub-step)
         assert f["sgpr_spill_count"] <= (0 if which == "bf16" else 96), (name, f)
+        assert f["group_segment_fixed_size"] <= 160 * 1024, (name, f)
+        assert f.get("private_segment_fixed_size", 0) == 0, (name, f)
+
+
+def test_wide_tile_gemm_has_no_spills_and_fits_lds(tmp_path):
+    kernels = _metadata(tmp_path, os.path.join(build.CSRC, "gemm_wide.hip"))
+    wide = {n: f for n, f in kernels.items() if "k_gemm_wide" in n}
+    assert len(wide) == 6, sorted(kernels)  # three element types, gate/up and down
+    for name, f in wide.items():
+        assert f["vgpr_spill_count"] == 0, (name, f)
+        assert f["vgpr_count"] <= 256, (name, f)  # two wavefronts per SIMD
+        # to lanes of a VGPR, read per item (29 .. 70 of them)
+        assert f["sgpr_spill_count"] <= 96, (name, f)
         assert f["group_segment_fixed_size"] <= 160 * 1024, (name, f)
         assert f.get("private_segment_fixed_size", 0) == 0, (name, f)
