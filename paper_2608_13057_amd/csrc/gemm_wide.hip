@@ -42,9 +42,9 @@
 //   items from the small end.  Row blocks of padding only are not computed.
 //   What whole rounds leave over goes by halves of items (one weight block of
 //   128 rows; four wavefront rows x two, three to seven slots of whole steps),
-//   but for fp8 gate/up, whose h scale spans both blocks: the last round is
-//   the small tiles', and a chip half filled with whole items waits for their
-//   latency.  Measured: 4097 tokens of 10 slots H 2048 I 1408, UE8M0 down 31.7
+//   but not in fp8 gate/up, whose h scale spans both blocks (halves of a tile's
+//   rows would keep it whole; not built): the last round is the small tiles',
+//   and a chip half filled with whole items waits for their latency.  Measured: 4097 tokens of 10 slots H 2048 I 1408, UE8M0 down 31.7
 //   -> 23.4 us; bf16 18 slots, 1499 tokens, gate/up 129 -> 123, 4096 rows of 512
 //   tokens down 61 -> 55, 11486 rows gate/up 295 -> 286.
 //   Items are never split: a row's sums run over its steps in order, so its

@@ -27,7 +27,8 @@ under profiles/).
 
 The traffic summary ends with a `traffic_json:` line that bench.py reads; it
 carries a hash of the stage-2 sources, and bench.py reports no traffic once
-the sources have changed since the counters were taken.
+the sources have changed since the counters were taken.  The matrix-pipe
+summaries and the fits of the stage-4 sweeps carry the same hash.
 """
 from __future__ import annotations
 
@@ -109,27 +110,17 @@ def fit_path(shape: str, dtype: str, m_tile: int) -> str:
 
 def committed_fit(shape: str, dtype: str, m_tile: int, scope: str = "gemm"):
     """The Eq. 1 fit (a, b, c, beta, n*) of a committed stage-4 profile for
-    one scope, or None: from its `fit_json:` line, else from the Eq. 1 row of
-    the scope's table."""
+    one scope, from its `fit_json:` line; None when there is none or the
+    stage-2 sources changed since the sweep."""
     path = fit_path(shape, dtype, m_tile)
     if not os.path.exists(path):
         return None
     with open(path) as fh:
-        text = fh.read()
-    for line in text.splitlines():
-        if line.startswith("fit_json: "):
-            d = json.loads(line[len("fit_json: "):])
-            if d.get("scope") == scope and d.get("model") == "Eq. 1":
-                return dict(d, source=os.path.relpath(path, ROOT))
-    sec = text.split(f"scope `{scope}`", 1)
-    if len(sec) < 2:
-        return None
-    for line in sec[1].splitlines():
-        if line.startswith("| Eq. 1 |"):
-            c = [x.strip() for x in line.strip("|").split("|")]
-            return {"scope": scope, "model": "Eq. 1", "a": float(c[1]), "b": float(c[2]), "c": float(c[3]),
-                    "beta": float(c[4]), "n_star": float(c[6]), "err_mean": float(c[7]), "err_max": float(c[8]),
-                    "source": os.path.relpath(path, ROOT)}
+        for line in fh:
+            if line.startswith("fit_json: "):
+                d = json.loads(line[len("fit_json: "):])
+                if d.get("scope") == scope and d.get("model") == "Eq. 1" and d.get("source_hash") == gemm_source_hash():
+                    return dict(d, source=os.path.relpath(path, ROOT))
     return None
 
 

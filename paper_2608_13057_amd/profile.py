@@ -25,6 +25,8 @@ import time
 
 import numpy as np
 
+from .measure import gemm_source_hash
+
 QWEN = dict(H=4096, I=1536)
 SHAPES = {"qwen3": QWEN, "dsv3": dict(H=7168, I=2048),  # expert shapes of the paper's two models
           "tiny": dict(H=256, I=512)}  # the tiny parity shape (harness tests)
@@ -148,10 +150,13 @@ def run_sweep(dtype="bf16", m_tile=128, Gs=DEFAULT_G, ns=DEFAULT_N, single_slot_
                 **SHAPES[shape])
     rows = []
     f = open(out, "a") if out else None
+    src = gemm_source_hash()
     pts = [(G, n) for G in Gs for n in ns] + [(1, n) for n in single_slot_ns]
     t0 = time.perf_counter()
     for k, (G, n) in enumerate(pts):
         r = h.point(G, n, reps=reps if (G, n) not in set((1, m) for m in single_slot_ns) else min(reps, 10))
+        for x in r:
+            x["source_hash"] = src
         rows += r
         if f:
             for x in r:
@@ -195,6 +200,8 @@ def markdown(rows, title: str, command: str, ns=DEFAULT_N) -> str:
     """A summary of a sweep: the fits of Eq. 1 / Eq. 2 per scope, the grid of
     stage-2 times, and the single-slot staircase (every 16th point)."""
     grid = [r for r in rows if not (r["G"] == 1 and r["n"] not in ns)]
+    hashes = {r.get("source_hash") for r in rows}
+    src = hashes.pop() if len(hashes) == 1 else None  # of the stage-2 sources that were timed
     out = [f"# Stage-4 profile: {title}", "", "Commands (repo root, MI355X):", "", "```", command, "```", ""]
     for scope in ("gemm", "block"):
         if not any(r["scope"] == scope for r in grid):
@@ -213,7 +220,7 @@ def markdown(rows, title: str, command: str, ns=DEFAULT_N) -> str:
             b2 = "" if e.get("b2") is None else f"{e['b2']:.3f}"
             out.append(f"| {lab} | {e['a']:.2f} | {e['b']:.3f} | {e['c']:.2f} | {e['beta']:.5f} | {b2} | "
                        f"{e['n_star']:.1f} | {e['err_mean']:.3f} | {e['err_max']:.3f} | {e['iterations']} |")
-            fits.append(dict(scope=scope, model=lab, **{x: e[x] for x in ("a", "b", "c", "beta", "n_star", "err_mean",
+            fits.append(dict(scope=scope, model=lab, source_hash=src, **{x: e[x] for x in ("a", "b", "c", "beta", "n_star", "err_mean",
                                                                            "err_max")},
                              **({"b2": e["b2"]} if e.get("b2") is not None else {})))
         lo, med, hi = sm["b_ci95"]

@@ -174,3 +174,26 @@ def test_committed_summaries_match_their_sources():
             assert d["source_hash"] == measure.gemm_source_hash()
     b, current = measure.committed_traffic("qwen3_decode_bf16", 64)
     assert b is None or b > 0
+
+
+def test_fits_are_of_the_current_kernels(tmp_path, monkeypatch):
+    """The fit that the benchmark line attaches is the committed one of the
+    same shape, dtype and M-tile only while the stage-2 sources are those that
+    were timed; a summary of rows from two builds belongs to neither."""
+    from paper_2608_13057_amd import profile
+
+    rows = [dict(scope=sc, G=G, n=n, N=G * n, tiles=G * -(-n // 64), t_us=20.0 + 5.0 * G + 0.1 * G * n, p10=1.0, p90=1.0,
+                 source_hash=measure.gemm_source_hash())
+            for sc in ("gemm", "block") for G in range(1, 9) for n in (1, 8, 64, 128, 512, 1024)]
+    path = tmp_path / "stage4.md"
+    monkeypatch.setattr(measure, "fit_path", lambda *a: str(path))
+
+    def fit(rows):
+        path.write_text(profile.markdown(rows, "t", "c"))
+        return measure.committed_fit("qwen3", "bf16", 64)
+
+    f = fit(rows)
+    assert f is not None and f["scope"] == "gemm" and f["model"] == "Eq. 1" and f["a"] > 0
+    assert fit([dict(r, source_hash="0" * 16) for r in rows]) is None
+    assert fit([{k: v for k, v in r.items() if k != "source_hash"} for r in rows]) is None
+    assert fit(rows[:-1] + [dict(rows[-1], source_hash="0" * 16)]) is None
