@@ -44,8 +44,9 @@
 //   128 rows; four wavefront rows x two, three to seven slots of whole steps),
 //   but not in fp8 gate/up, whose h scale spans both blocks (halves of a tile's
 //   rows would keep it whole; not built): the last round is the small tiles',
-//   and a chip half filled with whole items waits for their latency.  Measured: 4097 tokens of 10 slots H 2048 I 1408, UE8M0 down 31.7
-//   -> 23.4 us; bf16 18 slots, 1499 tokens, gate/up 129 -> 123, 4096 rows of 512
+//   and a chip half filled with whole items waits for their latency.
+//   Measured: 4097 tokens of 10 slots H 2048 I 1408, UE8M0 down 31.7 -> 23.4
+//   us; bf16 18 slots, 1499 tokens, gate/up 129 -> 123, 4096 rows of 512
 //   tokens down 61 -> 55, 11486 rows gate/up 295 -> 286.
 //   Items are never split: a row's sums run over its steps in order, so its
 //   result depends on its own inputs alone.
@@ -1058,7 +1059,7 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 // leave slots of very different sizes, which the other kernel balances worst;
 // a plan that keeps few replicas busy leaves it slots of few rows each, its
 // best case.  The lines lie where the plans together gain and the worst of them
-// loses little (of 1970 measured points inside them, 9 take over 3% more than with
+// loses little (of 2016 measured points inside them, 12 take over 3% more than with
 // the kernels before the wide tiles, at most 9%: fp8, 64-row tiles, 12 to 16
 // rows, fewest replicas on one of two placements).
 // Measured, forward us, other kernel -> wide tiles, uniform plan / token
@@ -1079,9 +1080,10 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 //          231 -> 200; 512: 562 -> 528 / 509 -> 451 / 385 -> 338; but full
 //          tiles that make about one round of items are its best case: (12b) 192
 //          [231]: 124 -> 138 / 114 -> 113 / 111 -> 85; 12 slots H 2048 I 768, 128
-//          [108]: 104 -> 93, 208 [126]: 110 -> 122, 288 [150]: 115 -> 125; 18
-//          slots H 4096 I 1024, 176 [240]: 214 -> 220, 256 [288]: 320 -> 237;
-//          (12a) 192 [336]: 233 -> 210 / 166 -> 182 / 157 -> 149, 320 [416]: 304
+//          [108]: 104 -> 93, 208 [126]: 110 -> 122, 288 [150]: 115 -> 125; with
+//          longer contractions only just: 18 slots H 4096 I 1024, 96 [192]: 198 ->
+//          195, 192 [248]: 214 -> 221, 256 [288]: 320 -> 237; (18) 64 [264]: 240 ->
+//          209 / 232 -> 202 / 195 -> 192; (12a) 192 [336]: 233 -> 210 / 166 -> 182 / 157 -> 149, 320 [416]: 304
 //          -> 265 / 232 -> 190 / 173 -> 181
 //   fp8    64-row tiles (18, two placements), 8: 102 -> 90 / 100 -> 90 / 95 ->
 //          84, 101 -> 91 / 100 -> 90 / 99 -> 91; 12: 107 -> 96 / 107 -> 96 / 103 ->
@@ -1091,15 +1093,14 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 //          300 -> 291; (12b) 64 [165]: 89 -> 79 / 82 -> 74 / 64 -> 72;
 //          (10) 96 [143]: 95 -> 85 / 90 -> 82 / 67 -> 78.  128-row tiles (18), 12:
 //          121 -> 95 / 112 -> 95 / 102 -> 87; 20 slots H 2048 I 512, 64 [100]: 77
-//          -> 84.  256-row tiles (18), 16: 165 -> 100
-//          / 163 -> 99 / 135 -> 95; 12 slots H 7168 I 384, 32 [39]: 121 -> 132, 64:
+//          -> 84.  256-row tiles (18), 16: 165 -> 100 / 163 -> 99 / 135 -> 95; 12 slots H 7168 I 384, 32 [39]: 121 -> 132, 64:
 //          155 -> 147
 //   UE8M0  64-row tiles (18), 48 [252]: 147 -> 130 / 138 -> 126 / 110 -> 121; 64:
-//          149 -> 133 / 144 -> 130 / 118 -> 126; (12b) 128 [198]: 118 -> 84 / 86
-//          -> 81 / 69 -> 77; (36) 32: 475 -> 416 / 388 -> 394 / 325 -> 336.  128-row
-//          tiles (18), 56: 158 -> 130 / 142 -> 128 / 126 -> 122; (10) 128 [154]: 97
-//          -> 83 / 93 -> 81 / 70 -> 78.  256-row tiles with I an odd multiple of
-//          128: 6 slots H 4096 I 384, 64 [21]: 72 -> 77, 256 [36]: 96 -> 103, 512
+//          149 -> 133 / 144 -> 130 / 118 -> 126; (12b) 64 [165]: 83 -> 76 / 73 -> 71
+//          / 60 -> 69, 128 [198]: 118 -> 84 / 86 -> 81 / 69 -> 77; (36) 32: 475 ->
+//          416 / 388 -> 394 / 325 -> 336.  128-row tiles (18), 56: 158 -> 130 / 142
+//          -> 128 / 126 -> 122; (10) 128 [154]: 97 -> 83 / 93 -> 81 / 70 -> 78.
+//          256-row tiles with I an odd multiple of 128: 6 slots H 4096 I 384, 64 [21]: 72 -> 77, 256 [36]: 96 -> 103, 512
 //          [54]: 129 -> 112; 12 slots H 7168 I 384, 64 [45]: 128 -> 137; 10 slots
 //          H 5120 I 896, 64 [84]: 115 -> 112 / 109 -> 108 / 94 -> 102; 16 slots
 //          H 1152 I 768, 32 [108]: 68 -> 59; against its own 256-row kernel 160:
@@ -1111,12 +1112,15 @@ bool experts_wide_wanted(const tempo_moe_shape& s) {
   const long long items = (s.S + P * s.S / (256 * E)) * (s.I / 128);
   const bool m64 = s.m_tile == 64, m256 = s.m_tile == 256, many = items >= 500, deep = s.H >= 4096;
   if (s.dtype == TEMPO_BF16) {
-    if (m256) return P >= 24 * E && (s.H % 256 || P < 64 * E || items <= 120 || items >= (deep ? 270 : 500));
+    // (where the own large-tile kernel serves 256-row tiles, see above)
+    const bool one_round = deep ? P >= 256 * E && items > 128 && items <= 270
+                                : P >= 64 * E && items > 120 && items < 500;
+    if (m256) return P >= 24 * E && (s.H % 256 || !one_round);
     return items >= 150 && P >= (many ? 48 : deep ? 80 : 128) * E;
   }
   if (s.dtype == TEMPO_FP8_E4M3) return (m256 || items >= (m64 ? 170 : 130)) && P >= (m64 && !many ? 8 : 12) * E;
   if (m256) return items >= 60 && P >= 32 * E;
-  return items >= (m64 ? 200 : 150) && P >= 48 * E;
+  return items >= (m64 ? 170 : 150) && P >= 48 * E;
 }
 
 hipError_t launch_experts_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,

@@ -71,7 +71,8 @@ def test_kernel_name_is_the_librarys_choice(dtype, T, S, H, I, m_tile, route, na
     ("bf16", 128, 64, 128, 8, 18, 4096, 1536, False), ("bf16", 128, 80, 128, 8, 18, 4096, 1536, True),
     ("bf16", 128, 112, 64, 6, 12, 3072, 2048, False), ("bf16", 128, 160, 64, 6, 12, 3072, 2048, True),
     ("bf16", 256, 96, 128, 8, 20, 2048, 768, False), ("bf16", 256, 192, 64, 8, 12, 2048, 1408, False),
-    ("bf16", 256, 24, 64, 8, 12, 2048, 1408, True), ("bf16", 256, 512, 128, 8, 18, 4096, 1536, True),
+    ("bf16", 256, 24, 64, 8, 12, 2048, 1408, True), ("bf16", 256, 64, 128, 8, 18, 4096, 1536, True),
+    ("bf16", 256, 256, 128, 8, 12, 4096, 1280, False), ("bf16", 256, 512, 128, 8, 18, 4096, 1536, True),
     ("fp8", 64, 12, 128, 8, 18, 4096, 1024, False), ("fp8", 64, 96, 64, 6, 10, 2048, 1408, False),
     ("fp8", 64, 12, 128, 8, 18, 4096, 1536, True), ("fp8", 128, 12, 128, 8, 18, 4096, 1536, True),
     ("fp8mx", 64, 128, 64, 6, 10, 2048, 1408, False), ("fp8mx", 64, 48, 128, 8, 18, 4096, 1536, True),
