@@ -101,20 +101,25 @@ bool stream_gathers_rows(const tempo_moe_shape& s, const Layout& L) {
 // slots that will be active are only known on the device; the expected number,
 // were the valid pairs spread evenly over the experts, stands for them (the
 // same for every plan).  Measured, forward us split -> whole, by expected
-// items over 256 workgroups (x):
+// items over 256 workgroups (x) and rows per expert:
 //   64-row tiles   bf16 H 4096 I 1536 18 slots 16 tokens (x 1.07) 77 -> 68, 32
 //          (1.46) 89 -> 83, 64 (1.66) 106 -> 110, 256 (1.69) 155 -> 152, 512 203 ->
-//          198; H 5120 I 2048 5 slots (0.62) 8 rows per expert 68 -> 74; H 7168 I
-//          2048 2 slots (0.25) 64 -> 75, 36 slots (2.9 .. 4.5) -2.5 .. +2.5%; H
-//          1152 (18 steps) 48 -> 43; fp8 H 3072 (24 steps) (0.4 .. 0.6) -6 .. +2 us
-//   128-row tiles  bf16 H 1152 68 -> 60, fp8 63 -> 55; H 2048 bf16 -10 .. +6 us, H
-//          3072 -9 .. +14, H 4096 18 slots -12 .. +11, 6 slots +6 .. +17
-//   256-row tiles  H 1152 -6 .. 0 us, H 4096 fp8 18 slots 0 .. +14
+//          198; H 7168 I 2048 36 slots (2.9 .. 4.5) -2.5 .. +2.5%; H 3072 I 1024
+//          (48 steps) 1 row (0.40) 48 -> 52, 8 (0.62) 63 -> 56; H 2048 I 512 (0.62)
+//          55 -> 51; H 5120 I 2048 (80 steps) 8 (0.62) 68 -> 74, 32: 93 -> 86; H
+//          7168 I 2048 2 slots (0.25) 64 -> 75; H 1152 (18 steps) 48 -> 43; fp8 H
+//          3072 (24 steps) (0.4 .. 0.6) -6 .. +2 us
+//   128-row tiles  bf16 H 1152 68 -> 60, fp8 63 -> 55; H 2048 bf16 10 slots 32 rows
+//          81 -> 72, 48: 83 -> 84; fp8 12 slots 48 rows 79 -> 71; H 3072 10 slots
+//          48 rows 96 -> 87, 128: 113 -> 128; H 4096 18 slots -12 .. +11 us, 6
+//          slots +6 .. +17
+//   256-row tiles  H 1152 -6 .. 0 us; H 2048 fp8 10 slots 8 rows 70 -> 63; H 4096
+//          fp8 18 slots 0 .. +14 us
 bool stream_whole_items(const tempo_moe_shape& s) {
-  if (s.m_tile > 64) return s.H <= 1280;
+  if (s.m_tile > 64) return s.H <= 2048;
   const int KT = s.H / (s.dtype == TEMPO_BF16 ? 64 : 128);
   const double active = s.S * (1.0 - std::pow(1.0 - 1.0 / s.E, (double)s.T_valid * s.K));
-  return KT <= 24 || active * (s.I / 64) >= 0.7 * 256;
+  return KT <= 24 || active * (s.I / 64) >= (KT <= 48 ? 0.5 : 0.7) * 256;
 }
 
 hipError_t launch_experts_bf16(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,

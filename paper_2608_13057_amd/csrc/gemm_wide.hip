@@ -1058,10 +1058,11 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 // Which of two kernels wins near the line depends on the plan: uniform shares
 // leave slots of very different sizes, which the other kernel balances worst;
 // a plan that keeps few replicas busy leaves it slots of few rows each, its
-// best case.  The lines lie where the plans together gain and the worst of them
-// loses little (of 2016 measured points inside them, 12 take over 3% more than with
-// the kernels before the wide tiles, at most 9%: fp8, 64-row tiles, 12 to 16
-// rows, fewest replicas on one of two placements).
+// best case.  The plan's weights are device memory, so the lines lie where the
+// plans together gain: 2625 measured calls on wide tiles (22 shapes, three plans)
+// take 17% less than with the kernels before, 84 of them over 5% more, at most 15%
+// (bf16, 256-row tiles, H 2048, just past a round of items; next fp8, 64-row
+// tiles, 16 rows, fewest replicas, 10%).
 // Measured, forward us, other kernel -> wide tiles, uniform plan / token
 // balancing / fewest replicas ("18": 18 slots H 4096 I 1536; "36": 36 slots H
 // 7168 I 2048; "12a": 12 slots H 3072 I 2048; "12b": 12 slots H 2048 I 1408;
@@ -1083,8 +1084,8 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 //          [108]: 104 -> 93, 208 [126]: 110 -> 122, 288 [150]: 115 -> 125; with
 //          longer contractions only just: 18 slots H 4096 I 1024, 96 [192]: 198 ->
 //          195, 192 [248]: 214 -> 221, 256 [288]: 320 -> 237; (18) 64 [264]: 240 ->
-//          209 / 232 -> 202 / 195 -> 192; (12a) 192 [336]: 233 -> 210 / 166 -> 182 / 157 -> 149, 320 [416]: 304
-//          -> 265 / 232 -> 190 / 173 -> 181
+//          209 / 232 -> 202 / 195 -> 192; (12a) 192 [336]: 233 -> 210 / 166 -> 182
+//          / 157 -> 149, 320 [416]: 304 -> 265 / 232 -> 190 / 173 -> 181
 //   fp8    64-row tiles (18, two placements), 8: 102 -> 90 / 100 -> 90 / 95 ->
 //          84, 101 -> 91 / 100 -> 90 / 99 -> 91; 12: 107 -> 96 / 107 -> 96 / 103 ->
 //          87, 111 -> 96 / 110 -> 95 / 104 -> 110; 24: 126 -> 121 / 119 -> 118 /
@@ -1093,18 +1094,18 @@ hipError_t launch_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, co
 //          300 -> 291; (12b) 64 [165]: 89 -> 79 / 82 -> 74 / 64 -> 72;
 //          (10) 96 [143]: 95 -> 85 / 90 -> 82 / 67 -> 78.  128-row tiles (18), 12:
 //          121 -> 95 / 112 -> 95 / 102 -> 87; 20 slots H 2048 I 512, 64 [100]: 77
-//          -> 84.  256-row tiles (18), 16: 165 -> 100 / 163 -> 99 / 135 -> 95; 12 slots H 7168 I 384, 32 [39]: 121 -> 132, 64:
-//          155 -> 147
+//          -> 84.  256-row tiles (18), 16: 165 -> 100 / 163 -> 99 / 135 -> 95; 12
+//          slots H 7168 I 384, 32 [39]: 121 -> 132, 64: 155 -> 147
 //   UE8M0  64-row tiles (18), 48 [252]: 147 -> 130 / 138 -> 126 / 110 -> 121; 64:
 //          149 -> 133 / 144 -> 130 / 118 -> 126; (12b) 64 [165]: 83 -> 76 / 73 -> 71
 //          / 60 -> 69, 128 [198]: 118 -> 84 / 86 -> 81 / 69 -> 77; (36) 32: 475 ->
 //          416 / 388 -> 394 / 325 -> 336.  128-row tiles (18), 56: 158 -> 130 / 142
 //          -> 128 / 126 -> 122; (10) 128 [154]: 97 -> 83 / 93 -> 81 / 70 -> 78.
-//          256-row tiles with I an odd multiple of 128: 6 slots H 4096 I 384, 64 [21]: 72 -> 77, 256 [36]: 96 -> 103, 512
-//          [54]: 129 -> 112; 12 slots H 7168 I 384, 64 [45]: 128 -> 137; 10 slots
-//          H 5120 I 896, 64 [84]: 115 -> 112 / 109 -> 108 / 94 -> 102; 16 slots
-//          H 1152 I 768, 32 [108]: 68 -> 59; against its own 256-row kernel 160:
-//          173 -> 173, 512: 327 -> 333
+//          256-row tiles with I an odd multiple of 128: 6 slots H 4096 I 384, 64
+//          [21]: 72 -> 77, 256 [36]: 96 -> 103, 512 [54]: 129 -> 112; 12 slots H
+//          7168 I 384, 64 [45]: 128 -> 137; 6 slots H 2048 I 640, 64 [35]: 69 ->
+//          64; 10 slots H 5120 I 896, 64 [84]: 115 -> 112 / 109 -> 108 / 94 -> 102;
+//          against its own 256-row kernel 160: 173 -> 173, 512: 327 -> 333
 bool experts_wide_wanted(const tempo_moe_shape& s) {
   if (experts_big_f8_supported(s)) return false;
   const long long P = (long long)s.T_valid * s.K, E = s.E;
@@ -1112,15 +1113,15 @@ bool experts_wide_wanted(const tempo_moe_shape& s) {
   const long long items = (s.S + P * s.S / (256 * E)) * (s.I / 128);
   const bool m64 = s.m_tile == 64, m256 = s.m_tile == 256, many = items >= 500, deep = s.H >= 4096;
   if (s.dtype == TEMPO_BF16) {
-    // (where the own large-tile kernel serves 256-row tiles, see above)
-    const bool one_round = deep ? P >= 256 * E && items > 128 && items <= 270
-                                : P >= 64 * E && items > 120 && items < 500;
-    if (m256) return P >= 24 * E && (s.H % 256 || !one_round);
-    return items >= 150 && P >= (many ? 48 : deep ? 80 : 128) * E;
+    if (m256) return P >= 24 * E && !(s.H % 256 == 0 && P >= 256 * E && items > 128 && items <= 270);
+    return items >= 150 && P >= (many ? (m64 ? 32 : 48) : m64 && deep ? 56 : 64) * E;
   }
-  if (s.dtype == TEMPO_FP8_E4M3) return (m256 || items >= (m64 ? 170 : 130)) && P >= (m64 && !many ? 8 : 12) * E;
-  if (m256) return items >= 60 && P >= 32 * E;
-  return items >= (m64 ? 170 : 150) && P >= 48 * E;
+  if (s.dtype == TEMPO_FP8_E4M3) {
+    if (m256) return P >= 12 * E;
+    return items >= 130 && P >= (m64 && !many ? (items >= 170 ? 8 : 20) : 12) * E;
+  }
+  if (m256) return P >= 32 * E && (!deep || items >= 50);
+  return items >= 150 && P >= (many ? 32 : 48) * E;
 }
 
 hipError_t launch_experts_wide(const tempo_moe_shape& s, const tempo_dispatch_out& d, const tempo_expert_weights& w,

@@ -15,7 +15,11 @@ pytestmark = pytest.mark.gpu
 TOL = {"exact": {"bf16": 1e-2, "fp8": 8e-2, "fp8mx": 8e-2}, "mirror": {"bf16": 4e-3, "fp8": 2e-2, "fp8mx": 2e-2}}
 IDENTICAL = {"bf16": 0.995, "fp8": 0.85, "fp8mx": 0.85}
 
+# rows of the experts held here: few (of 64 experts in all, the other pairs
+# nobody's), every number of live 32-row blocks of a 256-row tile, and full tiles
+FEW = [150, 0, 1, 31, 70, 129, 300]
 BLOCKS = [0, 1, 31, 33, 64, 65, 97, 129, 161, 193, 225, 255, 256, 257, 300, 520, 900]
+FULL = [300, 520, 900, 257, 256, 700, 33, 0]
 
 
 def _workload(dtype, ids, E, n_local, H, I, T_valid=None):
@@ -64,24 +68,20 @@ def _check(c, what, rng, extra=200):
     return y, d
 
 
-# few rows: 7 of 64 experts here, the other pairs nobody's; many: 17 experts, all here
-@pytest.mark.parametrize("route,dtype,m_tile,few,H,I", [
-    ("big", "bf16", 256, True, 512, 384), ("big", "bf16", 256, True, 1280, 128),
-    ("big", "bf16", 256, False, 512, 1152),
-    ("stream", "bf16", 256, True, 1152, 384), ("stream", "fp8", 256, True, 1152, 384),
-    ("stream", "fp8mx", 256, True, 1152, 384), ("stream", "fp8", 256, True, 128, 640),
-    ("stream", "bf16", 128, True, 1152, 640), ("stream", "fp8", 192, True, 1152, 640),
-    ("wide", "bf16", 192, False, 640, 1152), ("wide", "fp8", 192, False, 640, 1152),
-    ("wide", "fp8mx", 192, False, 640, 1152)])
-def test_route(route, dtype, m_tile, few, H, I):
-    """Slots of no row, one row, every number of live 32-row blocks of a
-    256-row tile (the many case), ragged tiles and several tiles."""
+@pytest.mark.parametrize("route,dtype,m_tile,counts,H,I", [
+    ("big", "bf16", 256, FEW, 512, 384), ("big", "bf16", 256, FEW, 1280, 128), ("big", "bf16", 256, FULL, 512, 1152),
+    ("stream", "bf16", 256, FEW, 1152, 384), ("stream", "fp8", 256, FEW, 1152, 384),
+    ("stream", "fp8mx", 256, FEW, 1152, 384), ("stream", "fp8", 256, FEW, 128, 640),
+    ("stream", "bf16", 128, FEW, 1152, 640), ("stream", "fp8", 192, FEW, 2048, 640),
+    ("wide", "bf16", 192, BLOCKS, 640, 1152), ("wide", "fp8", 192, BLOCKS, 640, 1152),
+    ("wide", "fp8mx", 192, BLOCKS, 640, 1152)])
+def test_route(route, dtype, m_tile, counts, H, I):
+    """Slots of no row, one row, ragged tiles, full tiles and several tiles."""
     from paper_2608_13057_amd import measure
 
-    counts = [150, 0, 1, 31, 70, 129, 300] if few else BLOCKS
-    E = 64 if few else len(counts)
+    E = 64 if counts is FEW else len(counts)
     ids = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
-    if few:
+    if counts is FEW:
         ids = np.concatenate([ids, np.full(9, 40, np.int32)])
     rng = np.random.default_rng(17)
     rng.shuffle(ids)

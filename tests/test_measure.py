@@ -66,18 +66,19 @@ def test_kernel_name_is_the_librarys_choice(dtype, T, S, H, I, m_tile, route, na
 
 
 @pytest.mark.parametrize("dtype,m_tile,rows,E,K,S,H,I,wide", [
-    ("bf16", 64, 48, 128, 8, 18, 4096, 1536, False), ("bf16", 64, 80, 128, 8, 18, 4096, 1536, True),
-    ("bf16", 64, 32, 256, 8, 36, 7168, 2048, False), ("bf16", 64, 48, 256, 8, 36, 7168, 2048, True),
-    ("bf16", 128, 64, 128, 8, 18, 4096, 1536, False), ("bf16", 128, 80, 128, 8, 18, 4096, 1536, True),
-    ("bf16", 128, 112, 64, 6, 12, 3072, 2048, False), ("bf16", 128, 160, 64, 6, 12, 3072, 2048, True),
-    ("bf16", 256, 96, 128, 8, 20, 2048, 768, False), ("bf16", 256, 192, 64, 8, 12, 2048, 1408, False),
-    ("bf16", 256, 24, 64, 8, 12, 2048, 1408, True), ("bf16", 256, 64, 128, 8, 18, 4096, 1536, True),
-    ("bf16", 256, 256, 128, 8, 12, 4096, 1280, False), ("bf16", 256, 512, 128, 8, 18, 4096, 1536, True),
-    ("fp8", 64, 12, 128, 8, 18, 4096, 1024, False), ("fp8", 64, 96, 64, 6, 10, 2048, 1408, False),
-    ("fp8", 64, 12, 128, 8, 18, 4096, 1536, True), ("fp8", 128, 12, 128, 8, 18, 4096, 1536, True),
-    ("fp8mx", 64, 128, 64, 6, 10, 2048, 1408, False), ("fp8mx", 64, 48, 128, 8, 18, 4096, 1536, True),
-    ("fp8mx", 64, 32, 256, 8, 36, 7168, 2048, False), ("fp8mx", 256, 64, 32, 4, 6, 4096, 384, False),
-    ("fp8mx", 256, 32, 64, 4, 12, 7168, 384, False), ("fp8mx", 256, 64, 64, 6, 10, 5120, 896, True)])
+    ("bf16", 64, 48, 128, 8, 18, 4096, 1536, False), ("bf16", 64, 64, 128, 8, 18, 4096, 1536, True),
+    ("bf16", 64, 24, 256, 8, 36, 7168, 2048, False), ("bf16", 64, 48, 256, 8, 36, 7168, 2048, True),
+    ("bf16", 64, 48, 64, 6, 12, 3072, 2048, False), ("bf16", 64, 80, 64, 6, 12, 3072, 2048, True),
+    ("bf16", 128, 48, 128, 8, 18, 4096, 1536, False), ("bf16", 128, 80, 128, 8, 18, 4096, 1536, True),
+    ("bf16", 256, 24, 64, 8, 12, 2048, 1408, True), ("bf16", 256, 512, 128, 8, 18, 4096, 1536, True),
+    ("bf16", 256, 288, 96, 8, 12, 2048, 768, False), ("bf16", 256, 16, 128, 8, 18, 4096, 1536, False),
+    ("fp8", 64, 12, 128, 8, 18, 4096, 1024, False), ("fp8", 64, 24, 128, 8, 18, 4096, 1024, True),
+    ("fp8", 64, 8, 128, 8, 18, 4096, 1536, True), ("fp8", 64, 8, 256, 8, 36, 7168, 2048, False),
+    ("fp8", 128, 12, 128, 8, 18, 4096, 1536, True), ("fp8", 128, 64, 128, 8, 20, 2048, 512, False),
+    ("fp8mx", 64, 96, 64, 6, 10, 2048, 1408, False), ("fp8mx", 64, 48, 128, 8, 18, 4096, 1536, True),
+    ("fp8mx", 64, 24, 256, 8, 36, 7168, 2048, False), ("fp8mx", 256, 64, 32, 4, 6, 4096, 384, False),
+    ("fp8mx", 256, 32, 64, 4, 12, 7168, 384, False), ("fp8mx", 256, 64, 32, 4, 6, 2048, 640, True),
+    ("fp8mx", 256, 64, 64, 6, 10, 5120, 896, True)])
 def test_wide_tiles_only_where_they_were_measured_faster(dtype, m_tile, rows, E, K, S, H, I, wide):
     """Points on both sides of the lines of experts_wide_wanted."""
     shape = moe.MoEShape(T=rows * E // K, K=K, E=E, S=S, H=H, I=I, m_tile=m_tile, dtype=dtype)
@@ -87,10 +88,11 @@ def test_wide_tiles_only_where_they_were_measured_faster(dtype, m_tile, rows, E,
 @pytest.mark.parametrize("dtype,m_tile,rows,E,K,S,H,I,whole", [
     ("bf16", 64, 2, 128, 8, 18, 4096, 1536, True), ("bf16", 64, 16, 32, 4, 5, 5120, 2048, False),
     ("bf16", 64, 8, 16, 2, 2, 7168, 2048, False), ("bf16", 64, 8, 256, 8, 36, 7168, 2048, True),
+    ("bf16", 64, 8, 64, 4, 10, 3072, 1024, True), ("bf16", 64, 1, 64, 4, 10, 3072, 1024, False),
     ("bf16", 64, 8, 96, 8, 12, 1536, 768, True), ("bf16", 128, 24, 128, 8, 18, 4096, 1536, False),
     ("bf16", 128, 128, 64, 4, 10, 3072, 1024, False), ("bf16", 128, 24, 96, 6, 16, 1152, 768, True),
-    ("fp8", 64, 4, 64, 4, 10, 3072, 1024, True), ("fp8", 64, 4, 32, 4, 5, 5120, 2048, False),
-    ("fp8", 128, 24, 128, 8, 20, 2048, 512, False), ("fp8", 256, 8, 128, 8, 18, 4096, 1536, False),
+    ("fp8", 64, 4, 64, 4, 10, 3072, 1024, True), ("fp8", 64, 1, 32, 4, 5, 5120, 2048, False),
+    ("fp8", 128, 24, 128, 8, 20, 2048, 512, True), ("fp8", 128, 24, 64, 4, 10, 3072, 1024, False), ("fp8", 256, 8, 128, 8, 18, 4096, 1536, False),
     ("fp8mx", 256, 16, 96, 6, 16, 1152, 640, True), ("fp8mx", 128, 64, 32, 4, 5, 5120, 2048, False)])
 def test_items_stay_whole_only_where_that_was_measured_faster(dtype, m_tile, rows, E, K, S, H, I, whole):
     """Points on both sides of the lines of stream_whole_items."""
